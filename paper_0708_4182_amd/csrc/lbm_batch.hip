@@ -271,6 +271,7 @@ hipError_t enqueue_step(lbm_batch *b, hipStream_t s, int slot, int parity, int g
     a.parity = parity;
     a.trt = b->trt ? 1 : 0;
     a.sround = b->sround ? 1 : 0;
+    a.rows = b->tile_rows;
     a.rng = b->d_rng;
     return lbm::launch_batch_step(b->storage, a, b->block_x, grid, s);
 }
@@ -286,6 +287,7 @@ hipError_t enqueue_stepk(lbm_batch *b, hipStream_t s, int parity) {
     a.parity = parity;
     a.trt = b->trt ? 1 : 0;
     a.sround = b->sround ? 1 : 0;
+    a.rows = b->tile_rows;
     a.rng = b->d_rng;
     return lbm::launch_batch_stepk(b->storage, a, b->kbx, b->kstep, s);
 }

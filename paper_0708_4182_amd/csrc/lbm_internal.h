@@ -84,6 +84,7 @@ struct BatchStepArgs {
     int32_t parity;            // index of the source buffer of every active channel
     int32_t trt;               // collision operator of every channel (Model::trt)
     int32_t sround;            // rounding of every channel (Model::sround)
+    int32_t rows;              // rows per tile asked for (multi-step kernel: selects its form)
     uint32_t *rng;             // two-slot step counter of stochastic rounding (slot parity is read)
 };
 

@@ -128,15 +128,21 @@ template <> __device__ __forceinline__ __bf16 bload<__bf16>(__amdgpu_buffer_rsrc
 __device__ __forceinline__ uint32_t bload_flag(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
     return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
 }
+template <int AUX = kStoreNT>
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float v) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)voff, (int)soff, kStoreNT);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)voff, (int)soff, AUX);
 }
+template <int AUX = kStoreNT>
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, _Float16 v) {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)voff, (int)soff, kStoreNT);
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)voff, (int)soff, AUX);
 }
+template <int AUX = kStoreNT>
 __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, __bf16 v) {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)voff, (int)soff, kStoreNT);
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)voff, (int)soff, AUX);
 }
+
+// A wave-uniform offset kept on the scalar side.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
 // Source offsets of the nine populations of node x under streaming with
 // halfway bounce-back (pull form).  fl holds the neighbour solid bits of x:
@@ -182,12 +188,16 @@ __device__ __forceinline__ void moments9(const float d[9], float &s, float &jx, 
 // -expm1(-x) in W. Kahan's form: with t = -x log2(e) and u = 2^t (the hardware's
 // base-2 exponential), expm1 = (u - 1) t / log2(u); the rounding error of u
 // appears in both factors and cancels, which keeps psi to a few ulp at any x.
-// u == 1 (|t| below half an ulp of 1) leaves the first-order term t ln 2.
+// u == 1 (|t| below half an ulp of 1) leaves the first-order term t ln 2, by a
+// select: both forms cost less than a branch around one of them.  Not
+// contracted: phi is the same whether a neighbour reads it from LDS or the
+// node uses it from a register.
 __device__ __forceinline__ float pseudopotential(const Model &m, float rho) {
+#pragma clang fp contract(off)
     const float t = -rho * m.log2e_inv_rho0;
     const float u = __builtin_amdgcn_exp2f(t);
-    const float em1 = u == 1.f ? t * 0.693147180559945309f
-                               : (u - 1.f) * (t * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(u)));
+    const float kahan = (u - 1.f) * (t * __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(u)));
+    const float em1 = u == 1.f ? t * 0.693147180559945309f : kahan;
     return -m.rho0 * em1;
 }
 
@@ -317,33 +327,32 @@ __device__ __forceinline__ void collide_mrt(const Model &m, const float d[9], fl
 }
 
 // Force, velocity shift (eq. (10)) and BGK collision (eq. (1)) of one node,
-// then the store of its nine post-collision populations.  phi of the 3x3
-// neighbourhood comes from LDS rows rowm (y-1), row0 (y), rowp (y+1) at
-// column c; solid neighbours hold phi = 0 there, which removes them from
-// eq. (5) as the model requires.
+// whose phi is pc and whose neighbours' phi are p1 .. p8 (e_1 .. e_8); solid
+// neighbours have phi = 0, which removes them from eq. (5) as the model
+// requires.  special (uniform for the wave): the flag word may hold anything;
+// otherwise the node has no solid neighbour and is outside the electric layer.
+// The fused multiply-adds are written out: every kernel rounds alike, whatever
+// its compiler would contract.
 template <bool TRT>
-__device__ __forceinline__ void collide_post(const Model &m, const float d[9], float s, float jx, float jy,
-                                             uint32_t fl, const float *rowm, const float *row0,
-                                             const float *rowp, int c, float out[9]) {
+__device__ __forceinline__ void collide_phi(const Model &m, const float d[9], float s, float jx, float jy,
+                                            bool special, uint32_t fl, float pc, float p1, float p2, float p3,
+                                            float p4, float p5, float p6, float p7, float p8, float out[9]) {
+#pragma clang fp contract(off)
     const float rho = m.rho_off + s;
-    const float pc = row0[c];
-    const float p1 = row0[c + 1], p3 = row0[c - 1];
-    const float p2 = rowp[c], p4 = rowm[c];
-    const float p5 = rowp[c + 1], p6 = rowp[c - 1], p7 = rowm[c - 1], p8 = rowm[c + 1];
     // eq. (5)
-    float sx = m.ga * (p1 - p3) + m.gd * ((p5 - p7) + (p8 - p6));
-    float sy = m.ga * (p2 - p4) + m.gd * ((p5 - p7) + (p6 - p8));
+    float sx = __builtin_fmaf(m.ga, p1 - p3, m.gd * ((p5 - p7) + (p8 - p6)));
+    float sy = __builtin_fmaf(m.ga, p2 - p4, m.gd * ((p5 - p7) + (p6 - p8)));
     // eq. (6): S(x + e_b) = bit (b-1) of fl
-    if (fl & 0xFFu) {
+    if (special && (fl & 0xFFu)) {
         const float s1 = (float)(fl & 1u), s2 = (float)((fl >> 1) & 1u), s3 = (float)((fl >> 2) & 1u),
                     s4 = (float)((fl >> 3) & 1u), s5 = (float)((fl >> 4) & 1u), s6 = (float)((fl >> 5) & 1u),
                     s7 = (float)((fl >> 6) & 1u), s8 = (float)((fl >> 7) & 1u);
-        sx += m.wa * (s1 - s3) + m.wd * ((s5 - s7) + (s8 - s6));
-        sy += m.wa * (s2 - s4) + m.wd * ((s5 - s7) + (s6 - s8));
+        sx += __builtin_fmaf(m.wa, s1 - s3, m.wd * ((s5 - s7) + (s8 - s6)));
+        sy += __builtin_fmaf(m.wa, s2 - s4, m.wd * ((s5 - s7) + (s6 - s8)));
     }
     float Fx = -pc * sx, Fy = -pc * sy;
     // electric force on the conductive part of the layer, n towards the electrode
-    if ((fl & FL_LAYER) && rho >= m.rho_c) {
+    if (special && (fl & FL_LAYER) && rho >= m.rho_c) {
         const uint32_t a = (fl >> FL_NSHIFT) & 15u;
         if (a == 0u) {
             Fy += (fl & FL_TOP) ? m.f_elec : -m.f_elec;
@@ -354,8 +363,8 @@ __device__ __forceinline__ void collide_post(const Model &m, const float d[9], f
         }
     }
     // driving body force
-    Fx += rho * m.gx;
-    Fy += rho * m.gy;
+    Fx = __builtin_fmaf(rho, m.gx, Fx);
+    Fy = __builtin_fmaf(rho, m.gy, Fy);
     if constexpr (TRT) {
         if (m.trt == 2) collide_mrt(m, d, rho, s, jx, jy, Fx, Fy, out);
         else collide_trt(m, d, rho, s, jx, jy, Fx, Fy, out);
@@ -363,10 +372,20 @@ __device__ __forceinline__ void collide_post(const Model &m, const float d[9], f
     }
     // eq. (10): rho u' = rho u + tau F
     float feq[9];
-    equilibrium(rho, s, jx + m.tau * Fx, jy + m.tau * Fy, feq);
+    equilibrium(rho, s, __builtin_fmaf(m.tau, Fx, jx), __builtin_fmaf(m.tau, Fy, jy), feq);
     const float om = m.omega;
 #pragma unroll
-    for (int a = 0; a < 9; ++a) out[a] = d[a] + om * (feq[a] - d[a]);
+    for (int a = 0; a < 9; ++a) out[a] = __builtin_fmaf(om, feq[a] - d[a], d[a]);
+}
+
+// The same with phi of the 3x3 neighbourhood from LDS rows rowm (y-1), row0
+// (y), rowp (y+1) at column c.
+template <bool TRT>
+__device__ __forceinline__ void collide_post(const Model &m, const float d[9], float s, float jx, float jy,
+                                             uint32_t fl, const float *rowm, const float *row0,
+                                             const float *rowp, int c, float out[9]) {
+    collide_phi<TRT>(m, d, s, jx, jy, true, fl, row0[c], row0[c + 1], rowp[c], row0[c - 1], rowm[c], rowp[c + 1],
+                     rowp[c - 1], rowm[c - 1], rowm[c + 1], out);
 }
 
 // The collision with its nine results encoded for storage (nearest).
@@ -719,6 +738,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8, 8))
 template <int K> struct Multi {
     static constexpr int H = 2 * K - 1;       // halo columns and rows per side
     static constexpr int FR = K == 2 ? 4 : 8; // flag ring rows (holds row a_{i-2(K-1)} while a_i is written)
+    static constexpr int FR32 = 8;            // of stepk_tile32 (holds rows a_{i-3K+2} .. a_i)
 };
 
 template <int S, int K>
@@ -938,7 +958,7 @@ __device__ __forceinline__ void stepk_tile(const StepArgs &a, int x0, int y0, in
                     collide_level(kc, up ? older : newer, mid, up ? newer : older, o);
                     const uint32_t prow = (uint32_t)pyr[k] * pitch;
 #pragma unroll
-                    for (int q = 0; q < 9; ++q) bstore(rd, v0, ((uint32_t)q * plane + prow) * E, o[q]);
+                    for (int q = 0; q < 9; ++q) bstore<0>(rd, v0, ((uint32_t)q * plane + prow) * E, o[q]);
                 }
             } else {
                 if (i >= 4 * k + 2 && !(pfl[k] & FL_SOLID)) {
@@ -963,8 +983,295 @@ __device__ __forceinline__ void stepk_tile(const StepArgs &a, int x0, int y0, in
     }
 }
 
-template <int S, bool TRT, bool SR, int BX, int K>
-__global__ void __launch_bounds__(BX) k_stepk(const StepArgs a) {
+// ---------------------------------------------------------------------------
+// The same K steps per launch for FP32 populations, in about 130 vector-ALU
+// instructions per node and step where stepk_tile spends 175 (per launch of
+// 8192 x 2048, K = 3, counting recomputed halo: 127 M against 139 M wave
+// instructions).  The arithmetic is stepk_tile's; what is taken off the
+// vector ALU is everything around it:
+// - The loop body is three iterations, so that the slots of the three-row
+//   rings are compile-time constants: LDS addresses are immediate offsets, and
+//   the rows carried in registers are renamed, not moved.
+// - Rows whose nodes all carry the plain flag word (a bit per row, see
+//   row_plain_mask: about 99% of the rows of the benchmark channel) run an
+//   instance of the iteration without any of the wall and electric-layer code,
+//   and load no flags.
+// - A level lags the one below by three rows instead of two, so that all it
+//   reads was written an iteration ago: two barriers per iteration, between
+//   them the pulls, then the collisions of all K levels as independent work
+//   (2K - 1 barriers, each waited for by one level, before).
+// - Every iteration issues nine loads and nine stores (rows and threads that
+//   store nothing get an offset past the buffer, which drops the store), so
+//   the wait for a row's loads counts past the stores behind them; loads and
+//   stores share one counter.
+// Registers (about 165) hold it at 3 waves per SIMD, LDS (67 KB at 256
+// columns, K = 3) at 2, which is why 16-bit storage, bound by vector-ALU issue
+// at 5 waves per SIMD, keeps stepk_tile: there this form measured 101 us per
+// step against 94 (FP16, K = 2) and 134 against 122 with stochastic rounding.
+// FP32: 131 -> 99 us per step (8192 x 2048, K = 3, 512 threads, chunks of 146
+// rows); TRT 153 -> 122.
+//
+// Iteration i of the march (rows a_0 .. upwards from y0 - H), for levels k = 0
+// .. K-1:
+//   pulls: row a_{i-3k} (level 0: from HBM, loaded one iteration ahead; level
+//   k: from the level k-1 rows a_{i-3k-1 .. i-3k+1} in LDS, bounce-back from
+//   the node's own results), rho and phi, phi to LDS;               barrier
+//   collisions: row a_{i-3k-1} with phi of rows a_{i-3k-2 .. i-3k} (the newest
+//   row's neighbours read from LDS, the others carried in registers), into LDS
+//   for level k + 1 or, at the last level, to HBM;                  barrier
+// Slot of row a_j in a ring: j mod 3.  A collision overwrites the row that the
+// pull before the barrier read last.
+template <int K>
+constexpr size_t multi32_lds_bytes(int bx) {
+    return (size_t)K * (bx + 2) * sizeof(float) + (size_t)(K - 1) * 3 * 9 * (bx + 2) * sizeof(float) +
+           (size_t)Multi<K>::FR32 * bx * sizeof(uint16_t);
+}
+
+template <bool TRT, int BX, int K>
+__device__ __forceinline__ void stepk_tile32(const StepArgs &a, int x0, int y0, int y1, char *lds) {
+    using std::integral_constant;
+    constexpr uint32_t E = sizeof(float);
+    constexpr int H = Multi<K>::H, FR = Multi<K>::FR32;
+    constexpr int P = BX + 2;   // LDS rows carry one padding slot per side (compile-time strides)
+    const Grid &g = a.g;
+    const Model &m = a.m;
+    const int tid = threadIdx.x;
+    const int nx = g.nx, ny = g.ny;
+    const uint32_t pitch = (uint32_t)g.pitch, plane = g.plane;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.src, 9u * plane * E);
+    const __amdgpu_buffer_rsrc_t rd = make_rsrc(a.dst, 9u * plane * E);
+    const __amdgpu_buffer_rsrc_t rf = make_rsrc(a.flags, plane * 2u);
+    const int nload = y1 - y0 + 2 * H;               // rows the march pulls from HBM
+    const int niter = nload + K - 1;                 // the last level ends K - 1 rows later
+
+    const int nact = min(BX - 2 * H, nx - x0);
+    int xc = (x0 - H + tid) % nx;
+    if (xc < 0) xc += nx;
+    const uint32_t x = (uint32_t)xc;
+    const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == (uint32_t)nx - 1 ? 0 : x + 1;
+    const uint32_t v0 = x * E, vm = xm * E, vp = xp * E;
+    // an offset past any buffer (they are all shorter): a store there is dropped
+    constexpr uint32_t kDrop = 0xFFFFFFF0u;
+    const uint32_t vs = tid >= H && tid < H + nact ? v0 : kDrop;
+
+    float *F = reinterpret_cast<float *>(lds);                       // level-k results [K-1][3][9][P]
+    float *psi = F + (K - 1) * 3 * 9 * P;                            // phi of the newest row of level k [K][P]
+    uint16_t *flr = reinterpret_cast<uint16_t *>(psi + K * P);       // flag words [FR][BX]
+    float *Ft = F + tid + 1, *psit = psi + tid + 1;
+    if (tid < 2) {      // padding slots (read only by threads whose results are unused)
+        const int side = tid ? P - 1 : 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) psi[k * P + side] = 0.f;
+#pragma unroll
+        for (int r = 0; r < (K - 1) * 3 * 9; ++r) F[r * P + side] = 0.f;
+    }
+
+    // rows of the march wrap around the lattice (more than once on the smallest)
+    auto row_mod = [&](int y) {
+        y %= ny;
+        return y < 0 ? y + ny : y;
+    };
+    auto next_row = [&](int y) { return y + 1 == ny ? 0 : y + 1; };
+    // plain bit of a row (uniform): the word of 32 rows is reloaded when the march leaves it
+    uint32_t pword = 0u;
+    int pindex = -1;
+    auto plain_row = [&](int yr) {
+        if ((yr >> 5) != pindex) {
+            pindex = yr >> 5;
+            pword = a.rowplain[pindex];
+        }
+        return (pword >> (yr & 31)) & 1u;
+    };
+    auto load_flags = [&](int yr) { return bload_flag(rf, x * 2u, (uint32_t)yr * pitch * 2u); };
+    auto issue_pops = [&](float (&c)[9], int yr, uint32_t fl, bool special) {
+        const int ym = yr == 0 ? ny - 1 : yr - 1, yp = yr == ny - 1 ? 0 : yr + 1;
+        const uint32_t r0 = (uint32_t)yr * pitch, rm = (uint32_t)ym * pitch, rp = (uint32_t)yp * pitch;
+        if (!special || __builtin_amdgcn_ballot_w64((fl & 0xFFu) != 0u) == 0) {
+            c[0] = bload<float>(rs, v0, uniform((0u * plane + r0) * E));
+            c[1] = bload<float>(rs, vm, uniform((1u * plane + r0) * E));
+            c[2] = bload<float>(rs, v0, uniform((2u * plane + rm) * E));
+            c[3] = bload<float>(rs, vp, uniform((3u * plane + r0) * E));
+            c[4] = bload<float>(rs, v0, uniform((4u * plane + rp) * E));
+            c[5] = bload<float>(rs, vm, uniform((5u * plane + rm) * E));
+            c[6] = bload<float>(rs, vp, uniform((6u * plane + rm) * E));
+            c[7] = bload<float>(rs, vp, uniform((7u * plane + rp) * E));
+            c[8] = bload<float>(rs, vm, uniform((8u * plane + rp) * E));
+        } else {
+            uint32_t o[9];
+            pull_offsets(fl & 0xFFu, plane, rm, r0, rp, xm, x, xp, o);
+#pragma unroll
+            for (int q = 0; q < 9; ++q) c[q] = bload<float>(rs, o[q] * E, 0u);
+        }
+    };
+
+    // per level, slot j mod 3 for row a_j: pulled populations (level 0 from
+    // their load on) and moments, phi with its west and east neighbours
+    float pd[K][3][9], ps[K][3], pjx[K][3], pjy[K][3], pc[K][3], pw[K][3], pe[K][3];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) pd[k][r][q] = 0.f;
+            ps[k][r] = pjx[k][r] = pjy[k][r] = pc[k][r] = pw[k][r] = pe[k][r] = 0.f;
+        }
+
+    // bit d of hist: row a_{i+2-d} is plain (rows before the march count as
+    // plain); an iteration concerns rows a_{i+1} .. a_{i-3K+2}
+    constexpr uint32_t WINDOW = (1u << (3 * K + 1)) - 1u;
+    uint32_t hist = ~0u;
+    int yload = row_mod(y0 - H), yflag = next_row(yload);    // rows a_{i+1}, a_{i+2}
+    uint32_t flw[3] = {0u, 0u, 0u};                          // flag words of rows a_i .. a_{i+2}, where not plain
+    hist = (hist << 1) | plain_row(yload);
+    if (!(hist & 1u)) flw[0] = load_flags(yload);
+    hist = (hist << 1) | plain_row(yflag);
+    if (!(hist & 1u)) flw[1] = load_flags(yflag);
+    issue_pops(pd[0][0], yload, flw[0], !((hist >> 1) & 1u));
+    // the nine stores that an iteration issues after its loads (dropped; nine
+    // places, so that they stay nine)
+    auto drop_stores = [&] {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) bstore<0>(rd, kDrop, (uint32_t)q * plane * E, 0.f);
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    drop_stores();
+    __builtin_amdgcn_sched_barrier(0);
+    int yk[K];                                               // row a_{i-3k-1}: the collision of level k
+#pragma unroll
+    for (int k = 0; k < K; ++k) yk[k] = row_mod(y0 - H - 3 * k - 1);
+
+    // one iteration; u = i mod 3 is the slot of rows a_{i-3k}; SLOW: rows with
+    // flags are concerned, or not every level has started
+    auto iteration = [&](auto uc, auto sc, int i) {
+        constexpr int u = decltype(uc)::value, mi = (u + 2) % 3, o = (u + 1) % 3;   // slots of rows -1, -2
+        constexpr bool SLOW = decltype(sc)::value;
+        auto flags_of = [&](int d) {                         // flag word of row a_{i-d}
+            uint32_t f = 0u;
+            if constexpr (SLOW) f = ((hist >> (d + 2)) & 1u) ? 0u : (uint32_t)flr[((i - d) & (FR - 1)) * BX + tid];
+            return f;
+        };
+        auto pull = [&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            const uint32_t fl = flags_of(3 * k);
+            float *d = pd[k][u];
+            if constexpr (k > 0) {
+                const float *Fb = Ft + (k - 1) * 3 * 9 * P;
+                const float *Fk = Fb + u * 9 * P, *Fm = Fb + mi * 9 * P, *Fp = Fb + o * 9 * P;
+                // population a from x - e_a, or (bounce-back) opp(a) of the node itself
+                float v[9] = {Fk[0 * P],     Fk[1 * P - 1], Fm[2 * P],     Fk[3 * P + 1], Fp[4 * P],
+                              Fm[5 * P - 1], Fm[6 * P + 1], Fp[7 * P + 1], Fp[8 * P - 1]};
+                if constexpr (SLOW) {
+                    if (__builtin_amdgcn_ballot_w64((fl & 0xFFu) != 0u) != 0) {
+                        v[1] = (fl & 0x04u) ? Fk[3 * P] : v[1];
+                        v[2] = (fl & 0x08u) ? Fk[4 * P] : v[2];
+                        v[3] = (fl & 0x01u) ? Fk[1 * P] : v[3];
+                        v[4] = (fl & 0x02u) ? Fk[2 * P] : v[4];
+                        v[5] = (fl & 0x40u) ? Fk[7 * P] : v[5];
+                        v[6] = (fl & 0x80u) ? Fk[8 * P] : v[6];
+                        v[7] = (fl & 0x10u) ? Fk[5 * P] : v[7];
+                        v[8] = (fl & 0x20u) ? Fk[6 * P] : v[8];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 9; ++q) d[q] = v[q];
+            }
+            moments9(d, ps[k][u], pjx[k][u], pjy[k][u]);
+            float p = pseudopotential(m, m.rho_off + ps[k][u]);
+            if constexpr (SLOW) p = (fl & FL_SOLID) ? 0.f : p;
+            pc[k][u] = p;
+            psit[k * P] = p;
+        };
+        auto collide_level = [&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            pw[k][u] = psit[k * P - 1];
+            pe[k][u] = psit[k * P + 1];
+            const uint32_t fl = flags_of(3 * k + 1);
+            float p[9];
+            collide_phi<TRT>(m, pd[k][mi], ps[k][mi], pjx[k][mi], pjy[k][mi], SLOW, fl, pc[k][mi], pe[k][mi], pc[k][u],
+                             pw[k][mi], pc[k][o], pe[k][u], pw[k][u], pw[k][o], pe[k][o], p);
+            if constexpr (k < K - 1) {
+                float *Fw = Ft + (k * 3 + mi) * 9 * P;
+#pragma unroll
+                for (int q = 0; q < 9; ++q) Fw[q * P] = p[q];
+            } else {
+                uint32_t vo = vs;
+                if constexpr (SLOW) vo = (fl & FL_SOLID) ? kDrop : vo;
+                const uint32_t rowoff = (uint32_t)yk[k] * pitch;
+#pragma unroll
+                for (int q = 0; q < 9; ++q) bstore<0>(rd, vo, uniform(((uint32_t)q * plane + rowoff) * E), p[q]);
+            }
+        };
+        // a level starts when the rows it needs exist: it pulls rows a_{2k} on
+        // and collides a_{2k+1} on; until then its slots hold nothing (and so
+        // need not be kept)
+        auto pull_if = [&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if (!SLOW || i >= 5 * k) {
+                pull(kc);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) pd[k][u][q] = 0.f;
+                ps[k][u] = pjx[k][u] = pjy[k][u] = pc[k][u] = 0.f;
+            }
+        };
+        auto collide_if = [&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if (!SLOW || i >= 5 * k + 2) {
+                collide_level(kc);
+            } else {
+                pw[k][u] = psit[k * P - 1];
+                pe[k][u] = psit[k * P + 1];
+                if constexpr (k == K - 1) drop_stores();
+            }
+        };
+        if constexpr (SLOW) {
+            if (!((hist >> 2) & 1u)) flr[(i & (FR - 1)) * BX + tid] = (uint16_t)flw[u];
+        }
+        pull(integral_constant<int, 0>{});
+        // the populations of row a_{i+1} (past the march's end the last row again)
+        issue_pops(pd[0][o], yload, flw[o], SLOW && !((hist >> 1) & 1u));
+        pull_if(integral_constant<int, 1>{});
+        if constexpr (K >= 3) pull_if(integral_constant<int, 2>{});
+        lds_barrier();
+        collide_if(integral_constant<int, 0>{});
+        collide_if(integral_constant<int, 1>{});
+        if constexpr (K >= 3) collide_if(integral_constant<int, 2>{});
+        lds_barrier();
+    };
+    auto step_row = [&](auto uc, int i) {
+        if (i + 1 < nload) yload = yflag;
+        if (i + 2 < nload) yflag = next_row(yflag);
+        hist = (hist << 1) | plain_row(yflag);
+        if (!(hist & 1u)) flw[(decltype(uc)::value + 2) % 3] = load_flags(yflag);
+        if ((hist & WINDOW) == WINDOW && i >= 5 * (K - 1) + 2) iteration(uc, std::false_type{}, i);
+        else iteration(uc, std::true_type{}, i);
+#pragma unroll
+        for (int k = 0; k < K; ++k) yk[k] = next_row(yk[k]);
+    };
+    for (int i = 0;; i += 3) {
+        step_row(integral_constant<int, 0>{}, i);
+        if (i + 1 >= niter) break;
+        step_row(integral_constant<int, 1>{}, i + 1);
+        if (i + 2 >= niter) break;
+        step_row(integral_constant<int, 2>{}, i + 2);
+        if (i + 3 >= niter) break;
+    }
+}
+
+// Waves per SIMD the compiler leaves registers for.
+template <bool TRT, bool TALL, int K> constexpr int stepk_waves = TALL ? (K == 3 ? 2 : TRT ? 3 : 4) : 4;
+
+// Rows per chunk from which FP32 launches run stepk_tile32 (TALL).  Its march
+// is faster per row (128 x 64 lattice, K = 3: 1.5 against 2.2 us per row of
+// one chunk), but its 40 KB of code arrive cold at every launch and its first
+// 12 rows run the slow instance: us per step at 8 / 16 / 32 / 64 / 128 rows, K =
+// 3, 256 threads, stepk_tile 23.7 / 20.6 / 31.0 / 55.4 / 105 and stepk_tile32 25.2 /
+// 22.8 / 29.3 / 45.7 / 78 on 2048 x 512; 59 / 55 / 62 / 64 / 107 and 59 / 52 / 55 / 56 /
+// 79 on 4096 x 1024.
+constexpr int TALL_ROWS = 32;
+
+template <int S, bool TRT, bool SR, int BX, int K, bool TALL = false>
+__global__ void __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(stepk_waves<TRT, TALL, K>))) k_stepk(const StepArgs a) {
     extern __shared__ char ldsk[];
     uint32_t mix[K];
 #pragma unroll
@@ -978,10 +1285,12 @@ __global__ void __launch_bounds__(BX) k_stepk(const StepArgs a) {
     }
     const int tile = (int)(blockIdx.x & 7u) * a.tiles_per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= a.ntiles) return;   // uniform for the workgroup, before any barrier
-    const int strip = tile / a.chunks, chunk = tile - strip * a.chunks;
+    const int strips = a.ntiles / a.chunks, chunk = tile / strips, strip = tile - chunk * strips;
     const int y0 = (int)(((int64_t)chunk * a.g.ny) / a.chunks);
     const int y1 = (int)(((int64_t)(chunk + 1) * a.g.ny) / a.chunks);
-    stepk_tile<S, TRT, SR, BX, K>(a, strip * (BX - 2 * Multi<K>::H), y0, y1, (chunk & 1) == 0, ldsk, mix);
+    const int x0 = strip * (BX - 2 * Multi<K>::H);
+    if constexpr (TALL) stepk_tile32<TRT, BX, K>(a, x0, y0, y1, ldsk);
+    else stepk_tile<S, TRT, SR, BX, K>(a, x0, y0, y1, (chunk & 1) == 0, ldsk, mix);
 }
 
 // ---------------------------------------------------------------------------
@@ -1744,8 +2053,8 @@ __global__ void __launch_bounds__(512) k_batch_tiles(const ChannelDesc *__restri
 // (strip * chunks_k + chunk) with strips of BX - 2H output columns.  With
 // stochastic rounding the K steps take the step counts count .. count + K - 1
 // and the next launch reads count + K, as in k_stepk.
-template <int S, bool TRT, bool SR, int BX, int K>
-__global__ void __launch_bounds__(BX) k_batch_tilesk(const ChannelDesc *__restrict__ descs,
+template <int S, bool TRT, bool SR, int BX, int K, bool TALL = false>
+__global__ void __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(stepk_waves<TRT, TALL, K>))) k_batch_tilesk(const ChannelDesc *__restrict__ descs,
                                                       const uint32_t *__restrict__ tiles, int ntiles,
                                                       int tiles_per_xcd, int parity, uint32_t *rng) {
     extern __shared__ char ldsk[];
@@ -1766,14 +2075,18 @@ __global__ void __launch_bounds__(BX) k_batch_tilesk(const ChannelDesc *__restri
     a.src = parity ? d->buf[1] : d->buf[0];
     a.dst = const_cast<void *>(parity ? d->buf[0] : d->buf[1]);
     a.flags = d->flags;
+    a.rowplain = d->rowplain;
     a.g = d->g;
     a.m = d->m;
     const int chunks = d->chunks_k;
     const int local = (int)(packed & 0xFFFFu);
-    const int strip = local / chunks, chunk = local - strip * chunks;
+    constexpr int COLS = BX - 2 * Multi<K>::H;
+    const int strips = (a.g.nx + COLS - 1) / COLS, chunk = local / strips, strip = local - chunk * strips;
     const int y0 = (int)(((int64_t)chunk * a.g.ny) / chunks);
     const int y1 = (int)(((int64_t)(chunk + 1) * a.g.ny) / chunks);
-    stepk_tile<S, TRT, SR, BX, K>(a, strip * (BX - 2 * Multi<K>::H), y0, y1, (chunk & 1) == 0, ldsk, mix);
+    const int x0 = strip * (BX - 2 * Multi<K>::H);
+    if constexpr (TALL) stepk_tile32<TRT, BX, K>(a, x0, y0, y1, ldsk);
+    else stepk_tile<S, TRT, SR, BX, K>(a, x0, y0, y1, (chunk & 1) == 0, ldsk, mix);
 }
 
 // Per-channel FP64 flux/mass reduction: one workgroup per channel, rows in
@@ -1879,10 +2192,11 @@ StepKernel stepk_k16(bool trt, bool sr) {
                : (sr ? k_stepk<S, false, true, BX, K> : k_stepk<S, false, false, BX, K>);
 }
 template <int BX, int K>
-StepKernel stepk_kernel_bx(int storage, bool trt, bool sr) {
+StepKernel stepk_kernel_bx(int storage, bool trt, bool sr, bool tall) {
     switch (storage) {
     case ST_F32:
         if (sr) return nullptr;
+        if (tall) return trt ? k_stepk<ST_F32, true, false, BX, K, true> : k_stepk<ST_F32, false, false, BX, K, true>;
         return trt ? k_stepk<ST_F32, true, false, BX, K> : k_stepk<ST_F32, false, false, BX, K>;
     case ST_F16: return stepk_k16<ST_F16, BX, K>(trt, sr);
     case ST_BF16: return stepk_k16<ST_BF16, BX, K>(trt, sr);
@@ -1890,39 +2204,52 @@ StepKernel stepk_kernel_bx(int storage, bool trt, bool sr) {
     }
 }
 template <int K>
-StepKernel stepk_kernel_k(int storage, int block_x, bool trt, bool sr) {
+StepKernel stepk_kernel_k(int storage, int block_x, bool trt, bool sr, bool tall) {
     switch (block_x) {
-    case 256: return stepk_kernel_bx<256, K>(storage, trt, sr);
-    case 512: return stepk_kernel_bx<512, K>(storage, trt, sr);
+    case 256: return stepk_kernel_bx<256, K>(storage, trt, sr, tall);
+    case 512: return stepk_kernel_bx<512, K>(storage, trt, sr, tall);
     default: return nullptr;
     }
 }
-StepKernel stepk_kernel(int storage, int block_x, int k, bool trt, bool sr) {
+StepKernel stepk_kernel(int storage, int block_x, int k, bool trt, bool sr, bool tall) {
     switch (k) {
-    case 2: return stepk_kernel_k<2>(storage, block_x, trt, sr);
-    case 3: return stepk_kernel_k<3>(storage, block_x, trt, sr);
+    case 2: return stepk_kernel_k<2>(storage, block_x, trt, sr, tall);
+    case 3: return stepk_kernel_k<3>(storage, block_x, trt, sr, tall);
     default: return nullptr;
     }
 }
-size_t stepk_lds_bytes(int storage, int block_x, int k) {
-    if (k == 3) return storage == ST_F32 ? multi_lds_bytes<ST_F32, 3>(block_x) : multi_lds_bytes<ST_F16, 3>(block_x);
-    return storage == ST_F32 ? multi_lds_bytes<ST_F32, 2>(block_x) : multi_lds_bytes<ST_F16, 2>(block_x);
+// LDS of a workgroup, of either form.
+template <int S, int K>
+size_t stepk_lds(int block_x, bool tall) {
+    return tall ? multi32_lds_bytes<K>(block_x) : multi_lds_bytes<S, K>(block_x);
+}
+size_t stepk_lds_of(int storage, int block_x, int k, bool tall) {
+    if (storage == ST_F32) return k == 3 ? stepk_lds<ST_F32, 3>(block_x, tall) : stepk_lds<ST_F32, 2>(block_x, tall);
+    return k == 3 ? stepk_lds<ST_F16, 3>(block_x, false) : stepk_lds<ST_F16, 2>(block_x, false);
+}
+// Whether chunks of `rows` rows run stepk_tile32.
+bool stepk_tall(int storage, int rows) { return storage == ST_F32 && rows >= TALL_ROWS; }
+
+size_t stepk_lds_bytes(int storage, int block_x, int k) {   // the larger form
+    return std::max(stepk_lds_of(storage, block_x, k, false), stepk_lds_of(storage, block_x, k, true));
 }
 
 hipError_t launch_stepk(int storage, const StepArgs &a, int block_x, int k, hipStream_t s) {
-    StepKernel kern = stepk_kernel(storage, block_x, k, a.m.trt != 0, a.m.sround != 0);
+    const bool tall = stepk_tall(storage, a.g.ny / a.chunks);
+    StepKernel kern = stepk_kernel(storage, block_x, k, a.m.trt != 0, a.m.sround != 0, tall);
     if (!kern || a.acc) return hipErrorInvalidValue;
     const unsigned blocks = 8u * (unsigned)a.tiles_per_xcd;
-    kern<<<blocks, block_x, stepk_lds_bytes(storage, block_x, k), s>>>(a);
+    kern<<<blocks, block_x, stepk_lds_of(storage, block_x, k, tall), s>>>(a);
     return hipGetLastError();
 }
 
 int stepk_blocks_per_cu(int storage, int block_x, int k, bool trt, bool sr) {
-    StepKernel kern = stepk_kernel(storage, block_x, k, trt, sr);
+    const bool tall = storage == ST_F32;
+    StepKernel kern = stepk_kernel(storage, block_x, k, trt, sr, tall);
     if (!kern) return 1;
     int n = 0;
     const hipError_t e =
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, block_x, stepk_lds_bytes(storage, block_x, k));
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, block_x, stepk_lds_of(storage, block_x, k, tall));
     return e == hipSuccess && n > 0 ? n : 1;
 }
 
@@ -2194,10 +2521,13 @@ BatchTilesKKernel batchk_k16(bool trt, bool sr) {
                : (sr ? k_batch_tilesk<S, false, true, BX, K> : k_batch_tilesk<S, false, false, BX, K>);
 }
 template <int BX, int K>
-BatchTilesKKernel batchk_kernel_bx(int storage, bool trt, bool sr) {
+BatchTilesKKernel batchk_kernel_bx(int storage, bool trt, bool sr, bool tall) {
     switch (storage) {
     case ST_F32:
         if (sr) return nullptr;
+        if (tall)
+            return trt ? k_batch_tilesk<ST_F32, true, false, BX, K, true>
+                       : k_batch_tilesk<ST_F32, false, false, BX, K, true>;
         return trt ? k_batch_tilesk<ST_F32, true, false, BX, K> : k_batch_tilesk<ST_F32, false, false, BX, K>;
     case ST_F16: return batchk_k16<ST_F16, BX, K>(trt, sr);
     case ST_BF16: return batchk_k16<ST_BF16, BX, K>(trt, sr);
@@ -2205,22 +2535,23 @@ BatchTilesKKernel batchk_kernel_bx(int storage, bool trt, bool sr) {
     }
 }
 template <int K>
-BatchTilesKKernel batchk_kernel_k(int storage, int block_x, bool trt, bool sr) {
+BatchTilesKKernel batchk_kernel_k(int storage, int block_x, bool trt, bool sr, bool tall) {
     switch (block_x) {
-    case 256: return batchk_kernel_bx<256, K>(storage, trt, sr);
-    case 512: return batchk_kernel_bx<512, K>(storage, trt, sr);
+    case 256: return batchk_kernel_bx<256, K>(storage, trt, sr, tall);
+    case 512: return batchk_kernel_bx<512, K>(storage, trt, sr, tall);
     default: return nullptr;
     }
 }
 
 hipError_t launch_batch_stepk(int storage, const BatchStepArgs &a, int block_x, int k, hipStream_t s) {
-    BatchTilesKKernel kern = k == 2 ? batchk_kernel_k<2>(storage, block_x, a.trt != 0, a.sround != 0)
-                           : k == 3 ? batchk_kernel_k<3>(storage, block_x, a.trt != 0, a.sround != 0)
+    const bool tall = stepk_tall(storage, a.rows);
+    BatchTilesKKernel kern = k == 2 ? batchk_kernel_k<2>(storage, block_x, a.trt != 0, a.sround != 0, tall)
+                           : k == 3 ? batchk_kernel_k<3>(storage, block_x, a.trt != 0, a.sround != 0, tall)
                                     : nullptr;
     if (!kern) return hipErrorInvalidValue;
     const int per = (a.ntiles + 7) / 8;
-    kern<<<8 * per, block_x, stepk_lds_bytes(storage, block_x, k), s>>>(a.descs, a.tiles, a.ntiles, per, a.parity,
-                                                                       a.rng);
+    kern<<<8 * per, block_x, stepk_lds_of(storage, block_x, k, tall), s>>>(a.descs, a.tiles, a.ntiles, per, a.parity,
+                                                                          a.rng);
     return hipGetLastError();
 }
 

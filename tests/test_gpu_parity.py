@@ -212,6 +212,29 @@ def test_multi_step_counts_and_calls(lbm, kernel, storage, nsteps):
         assert a.flux() == b.flux()
 
 
+@pytest.mark.parametrize("collision", [0, 1])
+@pytest.mark.parametrize("kernel,block_x,nx,ny,rows", [
+    ("three", 256, 246, 96, 32), ("three", 256, 247, 131, 33), ("three", 256, 31, 140, 140), ("three", 512, 503, 97, 97),
+    ("three", 512, 501, 64, 32), ("three", 256, 493, 127, 31), ("two", 256, 250, 98, 49), ("two", 256, 251, 132, 34),
+    ("two", 512, 505, 35, 35), ("two", 256, 499, 100, 50)])
+def test_tall_chunks_bitwise(lbm, kernel, block_x, nx, ny, rows, collision):
+    """Chunks of 32 rows and more run the multi-step kernel's other form in FP32:
+    strips one column short of, equal to and one over whole tiles, chunk heights
+    of every remainder of its three-row loop, just below and just above its
+    limit, with rough (slow) and open (fast) rows: bitwise the fused kernel."""
+    c = I.random_channel_case(nx=nx, ny=ny, seed=nx + rows)
+    c.params = c.params.replace(collision=collision)
+    a, b = lbm.from_case(c), lbm.from_case(c)
+    b.set_kernel(kernel)
+    b.set_tile(block_x, rows)
+    for n in (3, 16):
+        a.step(n)
+        b.step(n)
+        for x, y in zip(a.moments(), b.moments()):
+            np.testing.assert_array_equal(x, y)
+    assert a.flux() == b.flux()
+
+
 @pytest.mark.parametrize("kernel", ["split", "wide2", "wide4", "fused8", "two", "three"])
 def test_kernels_full_size(lbm, kernel):
     c = I.random_channel_case(nx=8192, ny=2048, seed=0)
