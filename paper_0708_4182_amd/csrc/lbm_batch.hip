@@ -10,7 +10,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <numeric>
 #include <string>
 #include <vector>
 
@@ -41,7 +40,7 @@ struct BatchLayout {
     std::vector<Grid> g;
     std::vector<size_t> buf0, buf1, flags, rowplain;
     size_t buf_bytes_max = 0;
-    size_t descs, tiles, tiles_k, counters, ids, cur, out, rng, total;
+    size_t descs, tiles, tiles_k, counters, cur, out, rng, total;
     size_t max_tiles;
 };
 
@@ -110,8 +109,6 @@ bool make_batch_layout(int n, const lbm_params *p, BatchLayout &L, std::string &
     off += align_up(4 * L.max_tiles, kAlign);
     L.counters = off;
     off += align_up(4 * kMaxGraphSteps, kAlign);
-    L.ids = off;
-    off += align_up(4 * (size_t)n, kAlign);
     L.cur = off;
     off += align_up(4 * (size_t)n, kAlign);
     L.out = off;
@@ -140,7 +137,7 @@ struct lbm_batch {
     uint32_t *d_tiles = nullptr;
     uint32_t *d_tiles_k = nullptr;     // tiles of the multi-step kernel
     uint32_t *d_counters = nullptr;
-    int32_t *d_ids = nullptr, *d_cur = nullptr;
+    int32_t *d_cur = nullptr;
     double *d_out = nullptr;
     size_t max_tiles = 0;
     hipStream_t stream = nullptr;
@@ -158,7 +155,6 @@ struct lbm_batch {
     int ntiles_k = 0;
     bool tiles_dirty = true;
     std::vector<uint32_t> host_tiles, host_tiles_k;
-    std::vector<int32_t> host_ids;
     int graph_steps = 0;
     int persistent = 0;                // 1: persistent queue kernel, 0: one workgroup per tile
     hipGraph_t graph[2] = {nullptr, nullptr};
@@ -407,7 +403,6 @@ lbm_status lbm_batch_init(lbm_batch **out, int32_t n, const lbm_params *p, const
     b->d_tiles = (uint32_t *)(ws + L.tiles);
     b->d_tiles_k = (uint32_t *)(ws + L.tiles_k);
     b->d_counters = (uint32_t *)(ws + L.counters);
-    b->d_ids = (int32_t *)(ws + L.ids);
     b->d_cur = (int32_t *)(ws + L.cur);
     b->d_out = (double *)(ws + L.out);
     b->d_rng = (uint32_t *)(ws + L.rng);
@@ -517,11 +512,10 @@ lbm_status lbm_batch_step(lbm_batch *b, int64_t nsteps) {
 lbm_status lbm_batch_flux(lbm_batch *b, double *Q, double *M) {
     lbm_status st = busable(b);
     if (st) return st;
-    b->host_ids.resize(b->n);
-    std::iota(b->host_ids.begin(), b->host_ids.end(), 0);
-    BHIP(b, hipMemcpyAsync(b->d_ids, b->host_ids.data(), 4 * (size_t)b->n, hipMemcpyHostToDevice, b->stream));
+    int ny_max = 0;
+    for (const Grid &g : b->g) ny_max = std::max(ny_max, g.ny);
     BHIP(b, hipMemcpyAsync(b->d_cur, b->cur.data(), 4 * (size_t)b->n, hipMemcpyHostToDevice, b->stream));
-    BHIP(b, lbm::launch_batch_reduce(b->storage, b->d_desc, b->d_ids, b->d_cur, b->n, b->d_out, b->stream));
+    BHIP(b, lbm::launch_batch_reduce(b->storage, b->d_desc, b->d_cur, b->n, ny_max, b->d_out, b->stream));
     std::vector<double> host(4 * (size_t)b->n);
     BHIP(b, hipMemcpyAsync(host.data(), b->d_out, 8 * host.size(), hipMemcpyDeviceToHost, b->stream));
     BHIP(b, hipStreamSynchronize(b->stream));

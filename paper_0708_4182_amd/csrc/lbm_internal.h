@@ -129,10 +129,11 @@ int batch_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
 // workgroup per tile of a.tiles (strips of block_x - 2(2k - 1) columns,
 // ChannelDesc::chunks_k chunks per strip); block_x 256 or 512.
 hipError_t launch_batch_stepk(int storage, const BatchStepArgs &a, int block_x, int k, hipStream_t s);
-// Per-channel FP64 reduction of channels ids[0..n): out[4*k] = Q, out[4*k+1] =
-// mass, out[4*k+2] = bad nodes, for the buffer index cur[ids[k]].
-hipError_t launch_batch_reduce(int storage, const ChannelDesc *descs, const int32_t *ids,
-                               const int32_t *cur, int n, double *out, hipStream_t s);
+// Per-channel FP64 reduction of n channels of at most ny_max rows: out[4*k] = Q,
+// out[4*k+1] = mass, out[4*k+2] = bad nodes of buffer cur[k] of channel k.
+// Uses the other buffer of every channel as scratch.
+hipError_t launch_batch_reduce(int storage, const ChannelDesc *descs, const int32_t *cur, int n, int ny_max,
+                               double *out, hipStream_t s);
 // FP64 reduction: out[0] = sum u_x, out[1] = sum rho, out[2] = number of bad
 // nodes; partials must hold 4 * max_reduce_blocks() doubles.
 int max_reduce_blocks();

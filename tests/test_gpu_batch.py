@@ -124,6 +124,23 @@ def test_batch_flux_matches_single(lbm):
         assert abs(Q[i] - q) <= 1e-12 * max(abs(q), 1e-12)
 
 
+@pytest.mark.parametrize("storage", [0, 1, 2])
+def test_batch_flux_is_bitwise_single(lbm, storage):
+    """One workgroup per row (per two rows above 1024) in the order of a single
+    lattice's reduction: the same bits for the lowest, ragged and tall channels
+    and an odd number of steps (either buffer is the spare one)."""
+    cases = [I.random_channel_case(nx=nx, ny=ny, seed=ny, storage=storage)
+             for nx, ny in ((5, 24), (257, 63), (64, 130), (70, 1024), (33, 1025))]
+    b = lbm.Batch(cases)
+    for n in (3, 4):
+        b.step(n)
+        Q, M = b.flux()
+        for i, c in enumerate(cases):
+            assert (Q[i], M[i]) == run_single(lbm, c, b.steps_done(i)).flux()
+        for x, y in zip(b.moments(0), run_single(lbm, cases[0], b.steps_done(0)).moments()):
+            np.testing.assert_array_equal(x, y)
+
+
 def test_batch_parity_vs_oracle(lbm):
     from test_gpu_parity import conductivity_margin
     cases = small_sweep(n=3, seed=21)
