@@ -473,14 +473,24 @@ int strip_columns(const lbm_sim *s, int kernel) {
     }
 }
 
+// Rows per workgroup of a rectangle launch of the kernel at the handle's tile;
+// 0: its launches march.
+int node_rows_for(const lbm_sim *s, int kernel) {
+    const int k = kernel == LBM_KERNEL_FUSED ? 1 : kernel == LBM_KERNEL_TWO ? 2 : 0;
+    return lbm::node_rows(s->p.storage, s->p.nx, s->p.ny, k, s->rows, s->cus);
+}
+
 // Launch arguments of a step kernel for the handle's current tile; `cache`
 // holds that kernel's row chunking (0 = recompute).
 lbm::StepArgs step_args_for(lbm_sim *s, int kernel, int &cache) {
-    const int cols = strip_columns(s, kernel);
+    const int node = node_rows_for(s, kernel);
+    const int cols = node ? lbm::node_columns(steps_per_launch(kernel)) : strip_columns(s, kernel);
     if (cache == 0) {
         const int strips = (s->p.nx + cols - 1) / cols;
         int chunks;
-        if (s->rows > 0) {
+        if (node) {
+            chunks = (s->p.ny + node - 1) / node;
+        } else if (s->rows > 0) {
             chunks = (s->p.ny + s->rows - 1) / s->rows;
         } else {
             // one wave of resident workgroups, chunks of at least 8 rows
@@ -516,6 +526,7 @@ lbm::StepArgs step_args_for(lbm_sim *s, int kernel, int &cache) {
     a.rng = s->rng;
     a.par = s->cur;
     a.acc = s->acc;
+    a.node = node;
     return a;
 }
 
@@ -872,6 +883,8 @@ lbm_status lbm_autotune(lbm_sim *s, int32_t reps, int32_t *block_x, int32_t *row
             s->rows = r;
             s->chunks = 0;
             s->chunks1 = 0;
+            // rectangle launches are the same at every tile: timed once
+            if (node_rows_for(s, cand.kernel) > 0 && (r > 0 || bx != 256)) continue;
             // trial launches read the current buffer and write the spare one,
             // so the state is left as it was
             lbm::StepArgs a = step_args(s);

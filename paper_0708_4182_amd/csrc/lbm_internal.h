@@ -59,6 +59,7 @@ struct StepArgs {
     // Per-node acceleration field [2][ny][nx] (x plane, then y plane), added
     // to (gx, gy); NULL for none (fused kernel, BGK, nearest rounding only).
     const float *acc;
+    int32_t node;              // rows per workgroup of a rectangle launch (chunks of them; 0: a march)
 };
 
 // One channel of a batch: its lattice, model and device arrays.
@@ -95,6 +96,11 @@ int step_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
 // The step kernel compiled for 8 waves per SIMD, and its resident workgroups.
 hipError_t launch_step8(int storage, const StepArgs &a, int block_x, hipStream_t s);
 int step8_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
+// Rows and columns that a workgroup of a rectangle launch (k_node) stores; 0
+// rows: the launch is a march.  k: steps per launch (0: a kernel that has no
+// such form); rows: rows per chunk asked for (0: automatic).
+int node_rows(int storage, int nx, int ny, int k, int rows, int cus);
+int node_columns(int k);
 // k = 2 or 3 time steps per launch (src -> dst after k steps; strips of
 // block_x - 2 (2k - 1) columns), its LDS per workgroup and its resident
 // workgroups per compute unit.

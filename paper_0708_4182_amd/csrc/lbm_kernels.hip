@@ -708,6 +708,217 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8, 8))
 }
 
 // ---------------------------------------------------------------------------
+// K = 1 or 2 time steps of a rectangle of nodes, one thread per node column
+// and R rows of it: no march, so a launch takes the latency of one pull plus K
+// collisions, where a march pays a round of loads and barriers per row.
+//
+// A wave holds 64 columns of R rows; the workgroup's eight waves stack to a tile
+// of NR = 8R rows.  With H = 2K - 1 halo columns and rows per side
+// (as in stepk_tile) it stores 64 - 2H columns of up to NR - 2H rows.  A thread
+// keeps its nodes through all levels: pulled populations, moments and flag
+// words stay in registers, phi and (below the last level) the encoded results
+// go through LDS, two barriers per level.  Rows that a level no longer needs
+// are skipped by whole waves.
+// The pulls are issued beside the flag words; a wave beside a wall then loads
+// the bounced-back populations in their place.  Bound by launch and memory
+// latency on small lattices (128 x 64, FP32: 3.4 us a launch at K = 1 and 4.3
+// at K = 2) and by vector-ALU issue and the halo (1.8 times the stored nodes
+// are pulled at K = 2, R = 2) on large ones.  us per step against the best march
+// of the same K: FP32 128 x 64 K = 2 2.1 (4.5), 1024 x 128 3.3 (6.5), 2048 x 768
+// 13.9 (16.5), TRT 3001 x 517 16.6 (18.9); BF16 2048 x 500 K = 1 11.5 (16.1).
+// R = 4 gained 7% in 16-bit storage at 2M nodes and lost 50% in FP32; K = 3 was
+// no faster anywhere.
+constexpr int NODE_BX = 512;
+template <int S, int K, int R> struct Node {
+    static constexpr int H = 2 * K - 1;
+    static constexpr int NR = R * NODE_BX / 64;
+    static constexpr int PAD = 64;                                 // floats in front of and behind phi and each F plane
+    static constexpr int PLANE = NR * 64 + 2 * PAD;
+    static constexpr size_t lds = PLANE * sizeof(float) + (K > 1 ? 9 * PLANE * sizeof(typename Codec<S>::T) : 0);
+};
+
+template <int S, bool TRT, bool SR, bool EXT, int K, int R>
+__device__ __forceinline__ void node_tile(const StepArgs &a, int x0, int y0, int y1, char *lds,
+                                          const uint32_t (&mix)[K]) {
+    using C = Codec<S>;
+    using T = typename C::T;
+    using N = Node<S, K, R>;
+    constexpr uint32_t E = sizeof(T);
+    constexpr int H = N::H, PLANE = N::PLANE;
+    const Grid &g = a.g;
+    const Model &m = a.m;
+    const int nx = g.nx, ny = g.ny;
+    const uint32_t pitch = (uint32_t)g.pitch, plane = g.plane;
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.src, 9u * plane * E);
+    const __amdgpu_buffer_rsrc_t rd = make_rsrc(a.dst, 9u * plane * E);
+    const __amdgpu_buffer_rsrc_t rf = make_rsrc(a.flags, plane * 2u);
+    const int lane = threadIdx.x & 63, row0 = (int)uniform(threadIdx.x >> 6) * R;
+    const bool out_col = lane >= H && lane < 64 - H && x0 - H + lane < nx;
+    int xc = (x0 - H + lane) % nx;
+    if (xc < 0) xc += nx;
+    const uint32_t x = (uint32_t)xc;
+    const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == (uint32_t)nx - 1 ? 0 : x + 1;
+    const uint32_t v0 = x * E, vm = xm * E, vp = xp * E;
+    float *phi = reinterpret_cast<float *>(lds) + N::PAD;
+    T *F = reinterpret_cast<T *>(lds + PLANE * sizeof(float)) + N::PAD;
+
+    // rows of the tile that exist (the chunk and its halo); rows below them are not computed
+    const int rows = y1 - y0 + 2 * H;
+    int yr[R];
+    uint32_t fl[R];
+    T raw[R][9];
+    float ax[R], ay[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        int y = (y0 - H + min(row0 + j, rows - 1)) % ny;
+        if (y < 0) y += ny;
+        yr[j] = y;
+        fl[j] = bload_flag(rf, x * 2u, (uint32_t)y * pitch * 2u);
+    }
+    // the plain pulls are issued beside the flag words, not behind them
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int y = yr[j], ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+        const uint32_t r0 = (uint32_t)y * pitch, rm = (uint32_t)ym * pitch, rp = (uint32_t)yp * pitch;
+        raw[j][0] = bload<T>(rs, v0, (0u * plane + r0) * E);
+        raw[j][1] = bload<T>(rs, vm, (1u * plane + r0) * E);
+        raw[j][2] = bload<T>(rs, v0, (2u * plane + rm) * E);
+        raw[j][3] = bload<T>(rs, vp, (3u * plane + r0) * E);
+        raw[j][4] = bload<T>(rs, v0, (4u * plane + rp) * E);
+        raw[j][5] = bload<T>(rs, vm, (5u * plane + rm) * E);
+        raw[j][6] = bload<T>(rs, vp, (6u * plane + rm) * E);
+        raw[j][7] = bload<T>(rs, vp, (7u * plane + rp) * E);
+        raw[j][8] = bload<T>(rs, vm, (8u * plane + rp) * E);
+        if constexpr (EXT) {
+            const size_t k = (size_t)y * (size_t)nx + (size_t)x;
+            ax[j] = a.acc[k];
+            ay[j] = a.acc[(size_t)nx * (size_t)ny + k];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        // beside a wall: the node's own opposite populations come back
+        if (__builtin_amdgcn_ballot_w64((fl[j] & 0xFFu) != 0u) != 0) {
+            const uint32_t own = (uint32_t)yr[j] * pitch + x;
+            T b[9];
+            auto opp = [&](int q, uint32_t bit, uint32_t o) {
+                if (fl[j] & bit) b[q] = bload<T>(rs, (o * plane + own) * E, 0u);
+                else b[q] = raw[j][q];
+            };
+            opp(1, 0x04u, 3u);
+            opp(2, 0x08u, 4u);
+            opp(3, 0x01u, 1u);
+            opp(4, 0x02u, 2u);
+            opp(5, 0x40u, 7u);
+            opp(6, 0x80u, 8u);
+            opp(7, 0x10u, 5u);
+            opp(8, 0x20u, 6u);
+#pragma unroll
+            for (int q = 1; q < 9; ++q) raw[j][q] = b[q];
+        }
+    }
+
+    float d[R][9], s[R], jx[R], jy[R];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        // level k: populations and phi of the rows [2k, rows - 2k)
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int r = row0 + j;
+            if (r < 2 * k || r >= rows - 2 * k) continue;
+            if (k == 0) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) d[j][q] = C::dec(raw[j][q]);
+            } else {
+                const T *f = F + r * 64 + lane;
+                if (__builtin_amdgcn_ballot_w64((fl[j] & 0xFFu) != 0u) == 0) {
+                    d[j][0] = C::dec(f[0]);
+                    d[j][1] = C::dec(f[1 * PLANE - 1]);
+                    d[j][2] = C::dec(f[2 * PLANE - 64]);
+                    d[j][3] = C::dec(f[3 * PLANE + 1]);
+                    d[j][4] = C::dec(f[4 * PLANE + 64]);
+                    d[j][5] = C::dec(f[5 * PLANE - 65]);
+                    d[j][6] = C::dec(f[6 * PLANE - 63]);
+                    d[j][7] = C::dec(f[7 * PLANE + 65]);
+                    d[j][8] = C::dec(f[8 * PLANE + 63]);
+                } else {
+                    auto from = [&](int q, int o, uint32_t bit, int off) {
+                        d[j][q] = C::dec(f[(fl[j] & bit) ? o * PLANE : q * PLANE + off]);
+                    };
+                    d[j][0] = C::dec(f[0]);
+                    from(1, 3, 0x04u, -1);
+                    from(2, 4, 0x08u, -64);
+                    from(3, 1, 0x01u, 1);
+                    from(4, 2, 0x02u, 64);
+                    from(5, 7, 0x40u, -65);
+                    from(6, 8, 0x80u, -63);
+                    from(7, 5, 0x10u, 65);
+                    from(8, 6, 0x20u, 63);
+                }
+            }
+            moments9(d[j], s[j], jx[j], jy[j]);
+            phi[r * 64 + lane] = (fl[j] & FL_SOLID) ? 0.f : pseudopotential(m, m.rho_off + s[j]);
+        }
+        lds_barrier();
+        // its collisions, rows [2k + 1, rows - 2k - 1)
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int r = row0 + j;
+            if (r < 2 * k + 1 || r >= rows - 2 * k - 1) continue;
+            const float *p = phi + r * 64 + lane;
+            float out[9];
+            Model mx = m;
+            if constexpr (EXT) {
+                mx.gx = m.gx + ax[j];
+                mx.gy = m.gy + ay[j];
+            }
+            collide_phi<TRT>(mx, d[j], s[j], jx[j], jy[j], true, fl[j], p[0], p[1], p[64], p[-1], p[-64], p[65],
+                             p[63], p[-65], p[-63], out);
+            T e[9];
+            if constexpr (SR) {
+                const uint32_t k0 = ((uint32_t)yr[j] * pitch + x) * 5u;
+                uint32_t h[5];
+#pragma unroll
+                for (int i = 0; i < 5; ++i) h[i] = lowbias32((k0 + (uint32_t)i) ^ mix[k]);
+#pragma unroll
+                for (int q = 0; q < 9; ++q) e[q] = C::enc_sr(out[q], (q & 1) ? (h[q >> 1] >> 16) : (h[q >> 1] & 0xFFFFu));
+            } else {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) e[q] = C::enc(out[q]);
+            }
+            if (k < K - 1) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) F[q * PLANE + r * 64 + lane] = e[q];
+            } else if (out_col && !(fl[j] & FL_SOLID)) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) bstore<0>(rd, v0, ((uint32_t)q * plane + (uint32_t)yr[j] * pitch) * E, e[q]);
+            }
+        }
+        if (k < K - 1) lds_barrier();
+    }
+}
+
+template <int S, bool TRT, bool SR, bool EXT, int K, int R>
+__global__ void __launch_bounds__(NODE_BX) k_node(const StepArgs a) {
+    extern __shared__ char ldsk[];
+    uint32_t mix[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) mix[k] = 0u;
+    if constexpr (SR) {
+        const uint32_t count = a.rng[a.par];
+        if (blockIdx.x == 0 && threadIdx.x == 0) a.rng[a.par ^ 1] = count + (uint32_t)K;
+#pragma unroll
+        for (int k = 0; k < K; ++k) mix[k] = lowbias32(count + (uint32_t)k + 0x9e3779b9u);
+    }
+    const int tile = (int)(blockIdx.x & 7u) * a.tiles_per_xcd + (int)(blockIdx.x >> 3);
+    if (tile >= a.ntiles) return;   // uniform for the workgroup, before any barrier
+    const int strips = a.ntiles / a.chunks, chunk = tile / strips, strip = tile - chunk * strips;
+    const int y0 = (int)(((int64_t)chunk * a.g.ny) / a.chunks);
+    const int y1 = (int)(((int64_t)(chunk + 1) * a.g.ny) / a.chunks);
+    node_tile<S, TRT, SR, EXT, K, R>(a, strip * (64 - 2 * Node<S, K, R>::H), y0, y1, ldsk, mix);
+}
+
+// ---------------------------------------------------------------------------
 // K time steps per launch (temporal blocking, K = 2 or 3).  A step moves every
 // population through HBM once each way; K steps in one pass move them once
 // for all K, with the intermediate post-collision rows kept in LDS in the
@@ -2163,6 +2374,68 @@ StepKernel step_kernel(int storage, bool trt, bool sr) {
     }
 }
 
+// Rectangles instead of a march where both population buffers fit the 256 MB
+// of Infinity Cache, which then serves the halo, and no tall chunk is asked
+// for.  us per step, rectangles against the best march: FP32 3072 x 1152 (255
+// MB) K = 1 41.3 / 57.3 and K = 2 25.8 / 26.7, FP16 3072 x 2304 (255 MB) 60.1 / 63.1
+// and 46 / 43; above, FP32 4096 x 1024 66.4 / 63.8 and 42.3 / 39.4.
+// The tile is 8 rows high while that leaves at most 3 (K = 1) or 2 workgroups per
+// compute unit, 16 above: us per step at 8 and 16 rows, K = 1: 1024 x 128 4.9 / 5.2,
+// 1024 x 256 6.4 / 6.9, FP16 1024 x 512 9.1 / 8.2; K = 2: 128 x 64 2.1 / 2.9, 512 x 96
+// 2.9 / 3.3, 1024 x 64 3.5 / 3.5, 1024 x 128 4.6 / 3.5.
+constexpr int64_t NODE_BYTES = 256000000;
+constexpr int NODE_ROWS = 16;
+int node_columns(int k) { return 64 - 2 * (2 * k - 1); }
+int node_rows(int storage, int nx, int ny, int k, int rows, int cus) {
+    const int64_t bytes = (int64_t)2 * 9 * nx * ny * (storage == ST_F32 ? 4 : 2);
+    if (k < 1 || k > 2 || rows > NODE_ROWS || bytes > NODE_BYTES) return 0;
+    const int halo = 2 * (2 * k - 1);
+    const int64_t strips = (nx + node_columns(k) - 1) / node_columns(k);
+    const int64_t tiles = strips * ((ny + 7 - halo) / (8 - halo));
+    return (tiles <= (int64_t)(k == 1 ? 3 : 2) * cus ? 8 : 16) - halo;
+}
+
+// A rectangle launch: the lowest tile that holds the chunks and their halo.
+template <int S, bool TRT, bool SR, bool EXT, int K, int R>
+hipError_t launch_node_r(const StepArgs &a, hipStream_t s) {
+    k_node<S, TRT, SR, EXT, K, R><<<8u * (unsigned)a.tiles_per_xcd, NODE_BX, Node<S, K, R>::lds, s>>>(a);
+    return hipGetLastError();
+}
+template <int S, bool TRT, bool SR, bool EXT, int K>
+hipError_t launch_node_k(const StepArgs &a, hipStream_t s) {
+    const int nr = (a.g.ny + a.chunks - 1) / a.chunks + 2 * Node<S, K, 1>::H;
+    if (nr <= Node<S, K, 1>::NR) return launch_node_r<S, TRT, SR, EXT, K, 1>(a, s);
+    if (nr <= Node<S, K, 2>::NR) return launch_node_r<S, TRT, SR, EXT, K, 2>(a, s);
+    return hipErrorInvalidValue;
+}
+template <int S, int K>
+hipError_t launch_node_s(const StepArgs &a, hipStream_t s) {
+    const bool sr = a.m.sround != 0;
+    if constexpr (S != ST_F32)
+        if (sr) return a.m.trt ? launch_node_k<S, true, true, false, K>(a, s)
+                               : launch_node_k<S, false, true, false, K>(a, s);
+    if (sr) return hipErrorInvalidValue;
+    return a.m.trt ? launch_node_k<S, true, false, false, K>(a, s) : launch_node_k<S, false, false, false, K>(a, s);
+}
+template <int K>
+hipError_t launch_node(int storage, const StepArgs &a, hipStream_t s) {
+    if (a.acc) {            // paper operator, nearest rounding, one step only (checked by the host)
+        if (K != 1 || a.m.trt || a.m.sround) return hipErrorInvalidValue;
+        switch (storage) {
+        case ST_F32: return launch_node_k<ST_F32, false, false, true, 1>(a, s);
+        case ST_F16: return launch_node_k<ST_F16, false, false, true, 1>(a, s);
+        case ST_BF16: return launch_node_k<ST_BF16, false, false, true, 1>(a, s);
+        default: return hipErrorInvalidValue;
+        }
+    }
+    switch (storage) {
+    case ST_F32: return launch_node_s<ST_F32, K>(a, s);
+    case ST_F16: return launch_node_s<ST_F16, K>(a, s);
+    case ST_BF16: return launch_node_s<ST_BF16, K>(a, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 template <bool EIGHT>
 hipError_t launch_step_k(int storage, const StepArgs &a, int block_x, hipStream_t s) {
     StepKernel k = step_kernel<EIGHT>(storage, a.m.trt != 0, a.m.sround != 0);
@@ -2179,6 +2452,7 @@ hipError_t launch_step_k(int storage, const StepArgs &a, int block_x, hipStream_
 }
 
 hipError_t launch_step(int storage, const StepArgs &a, int block_x, hipStream_t s) {
+    if (a.node) return launch_node<1>(storage, a, s);
     return launch_step_k<false>(storage, a, block_x, s);
 }
 
@@ -2233,6 +2507,7 @@ size_t stepk_lds_bytes(int storage, int block_x, int k) {   // the larger form
 }
 
 hipError_t launch_stepk(int storage, const StepArgs &a, int block_x, int k, hipStream_t s) {
+    if (a.node) return k == 2 ? launch_node<2>(storage, a, s) : hipErrorInvalidValue;
     const bool tall = stepk_tall(storage, a.g.ny / a.chunks);
     StepKernel kern = stepk_kernel(storage, block_x, k, a.m.trt != 0, a.m.sround != 0, tall);
     if (!kern || a.acc) return hipErrorInvalidValue;

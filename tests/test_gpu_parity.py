@@ -235,6 +235,42 @@ def test_tall_chunks_bitwise(lbm, kernel, block_x, nx, ny, rows, collision):
     assert a.flux() == b.flux()
 
 
+@pytest.mark.parametrize("nx,ny", [(5, 24), (58, 30), (59, 31), (62, 36), (63, 37), (124, 28), (300, 131), (1100, 140)])
+@pytest.mark.parametrize("storage,rounding,collision", [(0, 0, 0), (0, 0, 1), (0, 0, 2), (1, 0, 0), (1, 1, 1), (2, 0, 1),
+                                                        (2, 1, 0)])
+def test_rectangles_bitwise(lbm, storage, rounding, collision, nx, ny):
+    """Small lattices run rectangles of nodes (62 or 58 columns, 6 and 14 or 2 and
+    10 rows) unless chunks of more than 16 rows are asked for: whole tiles,
+    one over, a lattice narrower than a halo, 8- and 16-row tiles; bitwise the
+    one-step march, also with an acceleration field."""
+    import torch
+    c = I.random_channel_case(nx=nx, ny=ny, seed=nx + ny)
+    c.params = c.params.replace(storage=storage, rounding=rounding, collision=collision)
+    ref = lbm.from_case(c)
+    ref.set_tile(128, 17)
+    sims = []
+    for kernel in ("fused", "two"):
+        b = lbm.from_case(c)
+        b.set_kernel(kernel)
+        b.set_tile(256, 0)
+        sims.append(b)
+    for n in (3, 8):
+        ref.step(n)
+        for b in sims:
+            b.step(n)
+            for x, y in zip(ref.moments(), b.moments()):
+                np.testing.assert_array_equal(x, y)
+    assert all(b.flux() == ref.flux() for b in sims)
+    if rounding or collision:
+        return
+    acc = torch.from_numpy(1e-5 * np.random.default_rng(nx).standard_normal((2, ny, nx)).astype(np.float32)).cuda()
+    for b in (ref, sims[0]):
+        b.set_accel_field(acc)
+        b.step(5)
+    for x, y in zip(ref.moments(), sims[0].moments()):
+        np.testing.assert_array_equal(x, y)
+
+
 @pytest.mark.parametrize("kernel", ["split", "wide2", "wide4", "fused8", "two", "three"])
 def test_kernels_full_size(lbm, kernel):
     c = I.random_channel_case(nx=8192, ny=2048, seed=0)
