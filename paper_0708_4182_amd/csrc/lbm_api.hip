@@ -476,8 +476,11 @@ int strip_columns(const lbm_sim *s, int kernel) {
 // Rows per workgroup of a rectangle launch of the kernel at the handle's tile;
 // 0: its launches march.
 int node_rows_for(const lbm_sim *s, int kernel) {
-    const int k = kernel == LBM_KERNEL_FUSED ? 1 : kernel == LBM_KERNEL_TWO ? 2 : 0;
-    return lbm::node_rows(s->p.storage, s->p.nx, s->p.ny, k, s->rows, s->cus);
+    const int k = steps_per_launch(kernel);
+    if ((kernel != LBM_KERNEL_FUSED && kernel != LBM_KERNEL_TWO) ||
+        !lbm::node_fits((int64_t)18 * s->p.nx * s->p.ny * (int64_t)elem_size(s->p.storage), s->rows))
+        return 0;
+    return lbm::node_height(lbm::node_tiles8(s->p.nx, s->p.ny, k), k, s->cus);
 }
 
 // Launch arguments of a step kernel for the handle's current tile; `cache`

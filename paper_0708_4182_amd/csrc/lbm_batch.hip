@@ -149,6 +149,9 @@ struct lbm_batch {
     int parity = 0;                    // current buffer index of the active channels
     int block_x = 256;
     int tile_rows = 32;
+    bool tile_auto = true;             // no tile was asked for
+    int node1 = 0, nodek = 0;          // rows per workgroup of rectangle launches of one and of kstep steps (0: march)
+    int node1_tiles = 0, nodek_tiles = 0;   // their workgroups per channel
     int ntiles = 0;
     int kstep = 1;                     // time steps per launch: 1, or 2 / 3 (k_batch_tilesk)
     int kbx = 256;                     // block_x of the multi-step kernel (256 or 512)
@@ -218,18 +221,34 @@ lbm_status upload_tiles(lbm_batch *b) {
     });
     b->host_tiles.clear();
     b->host_tiles_k.clear();
+    // rectangle launches, where a single lattice of this size would run them
+    int64_t bytes = 0, tiles8 = 0, tiles8_k = 0;
+    for (int i : order) {
+        bytes += (int64_t)18 * b->g[i].nx * b->g[i].ny * (int64_t)elem_size(b->storage);
+        tiles8 += lbm::node_tiles8(b->g[i].nx, b->g[i].ny, 1);
+        tiles8_k += lbm::node_tiles8(b->g[i].nx, b->g[i].ny, 2);
+    }
+    const bool fits = lbm::node_fits(bytes, b->tile_auto ? 0 : b->tile_rows);
+    b->node1 = fits && !b->persistent ? lbm::node_height(tiles8, 1, b->cus) : 0;
+    b->nodek = fits && b->kstep == 2 ? lbm::node_height(tiles8_k, 2, b->cus) : 0;
+    b->node1_tiles = b->nodek_tiles = 0;
+    // a channel's chunks; its tiles, or for rectangles the channel, go to the list
+    auto list = [&](int i, int cols, int node, int &node_tiles, int32_t &chunks, std::vector<uint32_t> &out) {
+        const int strips = (b->g[i].nx + cols - 1) / cols;
+        chunks = node ? (b->g[i].ny + node - 1) / node : chunks_for(b->g[i].ny, b->tile_rows);
+        if (node) {
+            node_tiles = std::max(node_tiles, (strips * chunks + 7) / 8 * 8);
+            out.push_back((uint32_t)i);
+            return;
+        }
+        for (int t = 0; t < strips * chunks; ++t) out.push_back(((uint32_t)i << 16) | (uint32_t)t);
+    };
     const int kcols = b->kbx - 2 * (2 * std::max(b->kstep, 2) - 1);   // output columns of a multi-step strip
     for (int i : order) {
-        const int strips = (b->g[i].nx + b->block_x - 1) / b->block_x;
-        const int chunks = chunks_for(b->g[i].ny, b->tile_rows);
-        b->desc[i].chunks = chunks;
-        for (int t = 0; t < strips * chunks; ++t) b->host_tiles.push_back(((uint32_t)i << 16) | (uint32_t)t);
-        if (b->kstep > 1) {
-            const int kstrips = (b->g[i].nx + kcols - 1) / kcols;
-            b->desc[i].chunks_k = chunks;
-            for (int t = 0; t < kstrips * chunks; ++t)
-                b->host_tiles_k.push_back(((uint32_t)i << 16) | (uint32_t)t);
-        }
+        list(i, b->node1 ? lbm::node_columns(1) : b->block_x, b->node1, b->node1_tiles, b->desc[i].chunks, b->host_tiles);
+        if (b->kstep > 1)
+            list(i, b->nodek ? lbm::node_columns(2) : kcols, b->nodek, b->nodek_tiles, b->desc[i].chunks_k,
+                 b->host_tiles_k);
     }
     if (b->host_tiles.size() > b->max_tiles || b->host_tiles_k.size() > b->max_tiles)
         return bfail(b, LBM_EINVAL, "tile list overflow");
@@ -268,6 +287,8 @@ hipError_t enqueue_step(lbm_batch *b, hipStream_t s, int slot, int parity, int g
     a.trt = b->trt ? 1 : 0;
     a.sround = b->sround ? 1 : 0;
     a.rows = b->tile_rows;
+    a.node = b->node1;
+    a.node_tiles = b->node1_tiles;
     a.rng = b->d_rng;
     return lbm::launch_batch_step(b->storage, a, b->block_x, grid, s);
 }
@@ -284,6 +305,8 @@ hipError_t enqueue_stepk(lbm_batch *b, hipStream_t s, int parity) {
     a.trt = b->trt ? 1 : 0;
     a.sround = b->sround ? 1 : 0;
     a.rows = b->tile_rows;
+    a.node = b->nodek;
+    a.node_tiles = b->nodek_tiles;
     a.rng = b->d_rng;
     return lbm::launch_batch_stepk(b->storage, a, b->kbx, b->kstep, s);
 }
@@ -625,6 +648,7 @@ lbm_status lbm_batch_set_tile(lbm_batch *b, int32_t block_x, int32_t rows) {
     b->block_x = block_x;
     b->kbx = block_x == 512 ? 512 : 256;
     b->tile_rows = rows;
+    b->tile_auto = false;
     return upload_tiles(b);
 }
 
@@ -632,8 +656,7 @@ lbm_status lbm_batch_set_schedule(lbm_batch *b, int32_t persistent) {
     lbm_status st = busable(b);
     if (st) return st;
     b->persistent = persistent ? 1 : 0;
-    drop_graphs(b);
-    return LBM_OK;
+    return upload_tiles(b);      // the queue has no rectangle form
 }
 
 lbm_status lbm_batch_set_kernel(lbm_batch *b, int32_t kernel) {
@@ -703,7 +726,10 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t reps, int32_t *block_x, int3
             b->block_x = c.bx;
             b->kbx = c.bx == 512 ? 512 : 256;
             b->tile_rows = r;
+            b->tile_auto = false;
             if ((st = upload_tiles(b)) != LBM_OK) break;
+            // rectangle launches are the same at every tile: timed once
+            if ((c.kstep > 1 ? b->nodek : b->node1) && (c.bx != 256 || r != kRows[0])) continue;
             if ((c.kstep > 1 ? b->ntiles_k : b->ntiles) == 0) continue;
             const int grid = c.kstep > 1 ? 0 : persistent_grid(b);
             // trial launches read the current buffers and write the spare ones

@@ -86,6 +86,9 @@ struct BatchStepArgs {
     int32_t trt;               // collision operator of every channel (Model::trt)
     int32_t sround;            // rounding of every channel (Model::sround)
     int32_t rows;              // rows per tile asked for (multi-step kernel: selects its form)
+    int32_t node;              // rows per workgroup of a rectangle launch (0: a march); tiles then
+                               // holds the ntiles active channels
+    int32_t node_tiles;        // workgroups per channel, a multiple of 8
     uint32_t *rng;             // two-slot step counter of stochastic rounding (slot parity is read)
 };
 
@@ -96,11 +99,14 @@ int step_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
 // The step kernel compiled for 8 waves per SIMD, and its resident workgroups.
 hipError_t launch_step8(int storage, const StepArgs &a, int block_x, hipStream_t s);
 int step8_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
-// Rows and columns that a workgroup of a rectangle launch (k_node) stores; 0
-// rows: the launch is a march.  k: steps per launch (0: a kernel that has no
-// such form); rows: rows per chunk asked for (0: automatic).
-int node_rows(int storage, int nx, int ny, int k, int rows, int cus);
+// Rectangle launches (k_node, k_batch_node) of k = 1 or 2 steps: whether lattices
+// whose population buffers hold `bytes` run them when chunks of `rows` rows (0:
+// automatic) are asked for; the columns that a workgroup stores; and the rows,
+// from the number of tiles of the lowest height.
+bool node_fits(int64_t bytes, int rows);
 int node_columns(int k);
+int64_t node_tiles8(int nx, int ny, int k);
+int node_height(int64_t tiles8, int k, int cus);
 // k = 2 or 3 time steps per launch (src -> dst after k steps; strips of
 // block_x - 2 (2k - 1) columns), its LDS per workgroup and its resident
 // workgroups per compute unit.

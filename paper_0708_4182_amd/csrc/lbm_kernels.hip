@@ -2317,6 +2317,42 @@ __global__ void __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(stepk_w
     else stepk_tile<S, TRT, SR, BX, K>(a, x0, y0, y1, (chunk & 1) == 0, ldsk, mix);
 }
 
+// The batched step of 1 or 2 time steps by rectangles of nodes (node_tile):
+// channel ids[blockIdx.y], its tiles mapped to XCDs in contiguous ranges;
+// workgroups past a channel's tiles end at once.  Chosen as for a single
+// lattice, on the buffers of all active channels.  12 channels of the flux study
+// (FP32, 200 steps): 18 us per step by the best march, 6.3 so.
+template <int S, bool TRT, bool SR, int K, int R>
+__global__ void __launch_bounds__(NODE_BX) k_batch_node(const ChannelDesc *__restrict__ descs,
+                                                        const uint32_t *__restrict__ ids, int parity, uint32_t *rng) {
+    extern __shared__ char ldsk[];
+    uint32_t mix[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) mix[k] = 0u;
+    if constexpr (SR) {
+        const uint32_t count = rng[parity];
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) rng[parity ^ 1] = count + (uint32_t)K;
+#pragma unroll
+        for (int k = 0; k < K; ++k) mix[k] = lowbias32(count + (uint32_t)k + 0x9e3779b9u);
+    }
+    const ChannelDesc *d = descs + ids[blockIdx.y];
+    constexpr int COLS = 64 - 2 * Node<S, K, R>::H;
+    const int chunks = K == 1 ? d->chunks : d->chunks_k, strips = (d->g.nx + COLS - 1) / COLS;
+    const int ntiles = strips * chunks, per = (ntiles + 7) / 8;
+    const int tile = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || tile >= ntiles) return;    // uniform, before any barrier
+    StepArgs a;
+    a.src = parity ? d->buf[1] : d->buf[0];
+    a.dst = const_cast<void *>(parity ? d->buf[0] : d->buf[1]);
+    a.flags = d->flags;
+    a.g = d->g;
+    a.m = d->m;
+    const int chunk = tile / strips, strip = tile - chunk * strips;
+    const int y0 = (int)(((int64_t)chunk * a.g.ny) / chunks);
+    const int y1 = (int)(((int64_t)(chunk + 1) * a.g.ny) / chunks);
+    node_tile<S, TRT, SR, false, K, R>(a, strip * COLS, y0, y1, ldsk, mix);
+}
+
 // Per-channel FP64 flux/mass reduction: channel blockIdx.y, the rows and the
 // order of sums of a single lattice (k_reduce, k_reduce_final), so the results
 // are its bits.  The partials lie in the channel's spare population buffer,
@@ -2386,13 +2422,13 @@ StepKernel step_kernel(int storage, bool trt, bool sr) {
 constexpr int64_t NODE_BYTES = 256000000;
 constexpr int NODE_ROWS = 16;
 int node_columns(int k) { return 64 - 2 * (2 * k - 1); }
-int node_rows(int storage, int nx, int ny, int k, int rows, int cus) {
-    const int64_t bytes = (int64_t)2 * 9 * nx * ny * (storage == ST_F32 ? 4 : 2);
-    if (k < 1 || k > 2 || rows > NODE_ROWS || bytes > NODE_BYTES) return 0;
-    const int halo = 2 * (2 * k - 1);
-    const int64_t strips = (nx + node_columns(k) - 1) / node_columns(k);
-    const int64_t tiles = strips * ((ny + 7 - halo) / (8 - halo));
-    return (tiles <= (int64_t)(k == 1 ? 3 : 2) * cus ? 8 : 16) - halo;
+bool node_fits(int64_t bytes, int rows) { return bytes <= NODE_BYTES && rows <= NODE_ROWS; }
+int64_t node_tiles8(int nx, int ny, int k) {
+    const int rows = 8 - 2 * (2 * k - 1);
+    return (int64_t)((nx + node_columns(k) - 1) / node_columns(k)) * ((ny + rows - 1) / rows);
+}
+int node_height(int64_t tiles8, int k, int cus) {
+    return (tiles8 <= (int64_t)(k == 1 ? 3 : 2) * cus ? 8 : 16) - 2 * (2 * k - 1);
 }
 
 // A rectangle launch: the lowest tile that holds the chunks and their halo.
@@ -2759,7 +2795,36 @@ auto batch_kernel(int storage, bool trt, bool sr) -> decltype(batch_k<QUEUE, ST_
     }
 }
 
+template <int S, bool TRT, bool SR, int K>
+hipError_t launch_batch_node_k(const BatchStepArgs &a, hipStream_t s) {
+    const dim3 grid(a.node_tiles, a.ntiles);
+    if (a.node + 2 * Node<S, K, 1>::H <= Node<S, K, 1>::NR)
+        k_batch_node<S, TRT, SR, K, 1><<<grid, NODE_BX, Node<S, K, 1>::lds, s>>>(a.descs, a.tiles, a.parity, a.rng);
+    else if (a.node + 2 * Node<S, K, 2>::H <= Node<S, K, 2>::NR)
+        k_batch_node<S, TRT, SR, K, 2><<<grid, NODE_BX, Node<S, K, 2>::lds, s>>>(a.descs, a.tiles, a.parity, a.rng);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+template <int S, int K>
+hipError_t launch_batch_node_s(const BatchStepArgs &a, hipStream_t s) {
+    if constexpr (S != ST_F32)
+        if (a.sround) return a.trt ? launch_batch_node_k<S, true, true, K>(a, s)
+                                   : launch_batch_node_k<S, false, true, K>(a, s);
+    if (a.sround) return hipErrorInvalidValue;
+    return a.trt ? launch_batch_node_k<S, true, false, K>(a, s) : launch_batch_node_k<S, false, false, K>(a, s);
+}
+template <int K>
+hipError_t launch_batch_node(int storage, const BatchStepArgs &a, hipStream_t s) {
+    switch (storage) {
+    case ST_F32: return launch_batch_node_s<ST_F32, K>(a, s);
+    case ST_F16: return launch_batch_node_s<ST_F16, K>(a, s);
+    case ST_BF16: return launch_batch_node_s<ST_BF16, K>(a, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_batch_step(int storage, const BatchStepArgs &a, int block_x, int grid, hipStream_t s) {
+    if (a.node) return launch_batch_node<1>(storage, a, s);
     const size_t lds = (size_t)RING * (block_x + 2) * sizeof(float);
     const bool trt = a.trt != 0, sr = a.sround != 0;
     if (grid <= 0) {   // one workgroup per tile
@@ -2814,6 +2879,7 @@ BatchTilesKKernel batchk_kernel_k(int storage, int block_x, bool trt, bool sr, b
 }
 
 hipError_t launch_batch_stepk(int storage, const BatchStepArgs &a, int block_x, int k, hipStream_t s) {
+    if (a.node) return k == 2 ? launch_batch_node<2>(storage, a, s) : hipErrorInvalidValue;
     const bool tall = stepk_tall(storage, a.rows);
     BatchTilesKKernel kern = k == 2 ? batchk_kernel_k<2>(storage, block_x, a.trt != 0, a.sround != 0, tall)
                            : k == 3 ? batchk_kernel_k<3>(storage, block_x, a.trt != 0, a.sround != 0, tall)

@@ -212,6 +212,36 @@ def test_multi_step_batch_is_bitwise_single(lbm, kernel, storage, block_x):
         assert b.steps_done(i) == 61
 
 
+@pytest.mark.parametrize("kernel", ["fused", "two"])
+@pytest.mark.parametrize("storage,rounding,collision,tall", [(0, 0, 0, False), (0, 0, 1, True), (1, 1, 0, True),
+                                                             (2, 0, 2, False), (2, 1, 1, False)])
+def test_batch_rectangles_bitwise(lbm, kernel, storage, rounding, collision, tall):
+    """Small batches run rectangles of nodes (8 rows high, 16 with the tall
+    channels): bitwise the march that taller chunks ask for, with channels of
+    unlike sizes, a narrow one, odd step counts and one retired on the way."""
+    shapes = [(5, 24), (58, 33), (63, 37), (300, 131)] + ([(1200, 260), (700, 300)] if tall else [])
+    cases = []
+    for nx, ny in shapes:
+        c = I.random_channel_case(nx=nx, ny=ny, seed=nx)
+        c.params = c.params.replace(storage=storage, rounding=rounding, collision=collision)
+        cases.append(c)
+    a, b = lbm.Batch(cases), lbm.Batch(cases)
+    b.set_kernel(kernel)
+    a.set_tile(128, 17)
+    for n in (3, 6, 5):
+        a.step(n)
+        b.step(n)
+        for i in range(len(cases)):
+            for x, y in zip(a.moments(i), b.moments(i)):
+                np.testing.assert_array_equal(x, y, err_msg=f"channel {i}")
+        if n == 6:
+            gone = [i != 2 for i in range(len(cases))]
+            a.retire(gone)
+            b.retire(gone)
+    for x, y in zip(a.flux(), b.flux()):
+        np.testing.assert_array_equal(x, y)
+
+
 @pytest.mark.parametrize("kernel,graph_steps", [("two", 2), ("two", 10), ("three", 4), ("three", 10)])
 def test_multi_step_graph_equals_eager(lbm, kernel, graph_steps):
     """Replays of graphs of k-step launches plus single-step remainders (two
