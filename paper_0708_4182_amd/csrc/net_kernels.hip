@@ -16,6 +16,8 @@ namespace {
 template <class T> __device__ __forceinline__ float tof(T v) { return (float)v; }
 template <class T> __device__ __forceinline__ T fromf(float v) { return (T)v; }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // --------------------------------------------------------------- conv 3x3
 // One workgroup: 8 x 32 output pixels of one sample, 16 output channels.
 // Input channels are staged through LDS 8 at a time, with a one-pixel halo
@@ -428,30 +430,59 @@ __global__ void k_up_back(View dy, View dx, int N, int C) {
 }
 
 // ---------------------------------------------------------- 1x1 output
-template <class TA>
+// PX adjacent pixels per thread (one load per channel), four outputs per pass
+// over the input planes (the layer has 3), the sums in channel order.
+// Memory-bound, with the loads of 32 channels in flight and their weights in LDS
+// (as scalar loads the weights were a serial chain): 32 samples of 64 x 256, 32
+// channels 18 -> 10 us, one sample 14 -> 4.
+template <class TA, int PX>
 __global__ void k_conv1x1(View in, const float *__restrict__ w, const float *__restrict__ b, int N, int cin,
                           int cout, float *__restrict__ out) {
-    const size_t HW = (size_t)in.H * in.W;
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (size_t)N * HW) return;
+    typedef TA taN __attribute__((ext_vector_type(PX)));
+    typedef float floatN __attribute__((ext_vector_type(PX)));
+    constexpr int CB = 4 * sizeof(TA) * PX <= 32 ? 32 : 16;   // channels per pass, their weights in LDS
+    __shared__ f32x4 ws[CB];
+    const size_t HW = (size_t)in.H * in.W, total = (size_t)N * HW;
+    const size_t i0 = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * PX;
+    const size_t i = min(i0, total - PX);
     const size_t n = i / HW, p = i % HW;
     const TA *s = static_cast<const TA *>(in.p) + n * in.bs + p;
-    // four outputs per pass over the input planes (the layer has 3), the
-    // sums in channel order as before
     for (int o0 = 0; o0 < cout; o0 += 4) {
-        float acc[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[j] = o0 + j < cout ? b[o0 + j] : 0.f;
-#pragma unroll 8
-        for (int c = 0; c < cin; ++c) {
-            const float xc = tof(s[(size_t)c * HW]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (o0 + j < cout) acc[j] += w[(o0 + j) * cin + c] * xc;
-        }
+        float acc[4][PX];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (o0 + j < cout) out[(n * cout + o0 + j) * HW + p] = acc[j];
+#pragma unroll
+            for (int q = 0; q < PX; ++q) acc[j][q] = o0 + j < cout ? b[o0 + j] : 0.f;
+        for (int c0 = 0; c0 < cin; c0 += CB) {
+            const int nc = min(CB, cin - c0);
+            taN x[CB];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) x[c] = *reinterpret_cast<const taN *>(s + (size_t)(c0 + min(c, nc - 1)) * HW);
+            __syncthreads();
+            for (int e = threadIdx.x; e < 4 * CB; e += blockDim.x) {
+                const int c = c0 + (e >> 2), o = o0 + (e & 3);
+                reinterpret_cast<float *>(ws)[e] = c < cin && o < cout ? w[o * cin + c] : 0.f;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                if (c < nc) {
+                    const f32x4 wc = ws[c];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int q = 0; q < PX; ++q) acc[j][q] += wc[j] * tof((TA)x[c][q]);
+                }
+        }
+        if (i0 >= total) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (o0 + j < cout) {
+                floatN v;
+#pragma unroll
+                for (int q = 0; q < PX; ++q) v[q] = acc[j][q];
+                *reinterpret_cast<floatN *>(out + (n * cout + o0 + j) * HW + p) = v;
+            }
     }
 }
 
@@ -621,7 +652,6 @@ __global__ void k_zero(float *__restrict__ p, size_t n) {
 // halo (periodic x, zero y); the packed weights ([t][co][ci], see
 // k_pack_all) likewise.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int MH = 8, MCI = 32, MPS = 40;
 
 // Packed bf16 weights of every 3x3 matrix-core layer in one launch (workgroup
@@ -828,6 +858,72 @@ struct ConvLds {
     static constexpr int BYTES = IN_BYTES > OUT_BYTES ? IN_BYTES : OUT_BYTES;
 };
 
+// Output tile (CO planes of ROWS x TW values in LDS, plane stride OS) of sample n
+// to its planes, and its 2 x 2 means and 2x upsampling where asked for: each
+// lane stores 16 bytes of one row of one plane.
+template <class TO, int CO, int ROWS, int TW, int NT, int OS>
+__device__ __forceinline__ void conv_tile_out(const TO *os, TO *__restrict__ yo, const View &pool, const View &up,
+                                              int n, int cout, int co0, int H, int W, int tx0, int ty0, int tid) {
+            constexpr int EPP = 16 / (int)sizeof(TO), PPR = TW / EPP, PIECES = CO * ROWS * PPR;
+            const uint32_t HW = (uint32_t)(H * W);
+    #pragma unroll
+            for (int k = 0; k < (PIECES + NT - 1) / NT; ++k) {
+                const int e = tid + NT * k;
+                const int kk = e % PPR, row = (e / PPR) % ROWS, col = e / (PPR * ROWS);
+                const int y = ty0 + row, x = tx0 + kk * EPP, co = co0 + col;
+                if (e < PIECES && co < cout && y < H && x < W) {
+                    const uint4 v = *reinterpret_cast<const uint4 *>(&os[col * OS + row * TW + kk * EPP]);
+                    *reinterpret_cast<uint4 *>(yo + (uint32_t)co * HW + (uint32_t)(y * W + x)) = v;
+                    if constexpr (sizeof(TO) == 2) {
+                        if (up.p != nullptr) {
+                            // eight values -> sixteen (each twice) in rows 2 y and 2 y + 1
+                            auto dup = [](uint32_t w) {
+                                return make_uint2((w & 0xffffu) * 0x10001u, (w >> 16) * 0x10001u);
+                            };
+                            const uint2 d0 = dup(v.x), d1 = dup(v.y), d2 = dup(v.z), d3 = dup(v.w);
+                            const uint4 lo = make_uint4(d0.x, d0.y, d1.x, d1.y), hi = make_uint4(d2.x, d2.y, d3.x, d3.y);
+                            TO *uo = static_cast<TO *>(up.p) + (size_t)n * up.bs +
+                                     (size_t)co * ((uint32_t)up.H * (uint32_t)up.W) + (uint32_t)(2 * y * up.W + 2 * x);
+                            *reinterpret_cast<uint4 *>(uo) = lo;
+                            *reinterpret_cast<uint4 *>(uo + 8) = hi;
+                            *reinterpret_cast<uint4 *>(uo + up.W) = lo;
+                            *reinterpret_cast<uint4 *>(uo + up.W + 8) = hi;
+                        }
+                    }
+                }
+            }
+            if constexpr (sizeof(TO) == 2) {
+                if (pool.p != nullptr) {
+                    // eight pooled values (16 bytes) of one pooled row per piece,
+                    // from two 16-value runs of output rows 2 r and 2 r + 1
+                    constexpr int PPR2 = TW / 16, PP = CO * (ROWS / 2) * PPR2;
+                    const uint32_t HWo = (uint32_t)(pool.H * pool.W);
+                    TO *__restrict__ po = static_cast<TO *>(pool.p) + (size_t)n * pool.bs;
+    #pragma unroll
+                    for (int k = 0; k < (PP + NT - 1) / NT; ++k) {
+                        const int e = tid + NT * k;
+                        const int kk = e % PPR2, r = (e / PPR2) % (ROWS / 2), col = e / (PPR2 * (ROWS / 2));
+                        const int y = ty0 / 2 + r, x = tx0 / 2 + 8 * kk, co = co0 + col;
+                        if (e < PP && co < cout && y < pool.H && x < pool.W) {
+                            const TO *r0 = &os[col * OS + (2 * r) * TW + 16 * kk], *r1 = r0 + TW;
+                            uint32_t w4[4];
+    #pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const float a0 = 0.25f * ((tof(r0[4 * j]) + tof(r0[4 * j + 1])) +
+                                                          (tof(r1[4 * j]) + tof(r1[4 * j + 1])));
+                                const float a1 = 0.25f * ((tof(r0[4 * j + 2]) + tof(r0[4 * j + 3])) +
+                                                          (tof(r1[4 * j + 2]) + tof(r1[4 * j + 3])));
+                                w4[j] = (uint32_t)__builtin_bit_cast(unsigned short, fromf<TO>(a0)) |
+                                        (uint32_t)__builtin_bit_cast(unsigned short, fromf<TO>(a1)) << 16;
+                            }
+                            *reinterpret_cast<uint4 *>(po + (uint32_t)co * HWo + (uint32_t)(y * pool.W + x)) =
+                                make_uint4(w4[0], w4[1], w4[2], w4[3]);
+                        }
+                    }
+                }
+            }
+}
+
 // Input: bf16 activations (or the bf16 copy of the layer gradient); TO:
 // output type; bias may be NULL.  NM: 16-channel output tiles per workgroup
 // (4: 64 channels; 2: 32 channels).  VEC: see ConvStage; it also sends the
@@ -933,64 +1029,7 @@ __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, con
                     os[col * L::OS + pix] = fromf<TO>(v);
                 }
         __syncthreads();
-        constexpr int EPP = 16 / (int)sizeof(TO), PPR = TW / EPP, PIECES = CO * MH * PPR;
-        const uint32_t HW = (uint32_t)(H * W);
-#pragma unroll
-        for (int k = 0; k < (PIECES + NT - 1) / NT; ++k) {
-            const int e = tid + NT * k;
-            const int kk = e % PPR, row = (e / PPR) % MH, col = e / (PPR * MH);
-            const int y = ty0 + row, x = tx0 + kk * EPP, co = co0 + col;
-            if (e < PIECES && co < cout && y < H && x < W) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(&os[col * L::OS + row * TW + kk * EPP]);
-                *reinterpret_cast<uint4 *>(yo + (uint32_t)co * HW + (uint32_t)(y * W + x)) = v;
-                if constexpr (sizeof(TO) == 2) {
-                    if (up.p != nullptr) {
-                        // eight values -> sixteen (each twice) in rows 2 y and 2 y + 1
-                        auto dup = [](uint32_t w) {
-                            return make_uint2((w & 0xffffu) * 0x10001u, (w >> 16) * 0x10001u);
-                        };
-                        const uint2 d0 = dup(v.x), d1 = dup(v.y), d2 = dup(v.z), d3 = dup(v.w);
-                        const uint4 lo = make_uint4(d0.x, d0.y, d1.x, d1.y), hi = make_uint4(d2.x, d2.y, d3.x, d3.y);
-                        TO *uo = static_cast<TO *>(up.p) + (size_t)n * up.bs +
-                                 (size_t)co * ((uint32_t)up.H * (uint32_t)up.W) + (uint32_t)(2 * y * up.W + 2 * x);
-                        *reinterpret_cast<uint4 *>(uo) = lo;
-                        *reinterpret_cast<uint4 *>(uo + 8) = hi;
-                        *reinterpret_cast<uint4 *>(uo + up.W) = lo;
-                        *reinterpret_cast<uint4 *>(uo + up.W + 8) = hi;
-                    }
-                }
-            }
-        }
-        if constexpr (sizeof(TO) == 2) {
-            if (pool.p != nullptr) {
-                // eight pooled values (16 bytes) of one pooled row per piece,
-                // from two 16-value runs of output rows 2 r and 2 r + 1
-                constexpr int PPR2 = TW / 16, PP = CO * (MH / 2) * PPR2;
-                const uint32_t HWo = (uint32_t)(pool.H * pool.W);
-                TO *__restrict__ po = static_cast<TO *>(pool.p) + (size_t)n * pool.bs;
-#pragma unroll
-                for (int k = 0; k < (PP + NT - 1) / NT; ++k) {
-                    const int e = tid + NT * k;
-                    const int kk = e % PPR2, r = (e / PPR2) % (MH / 2), col = e / (PPR2 * (MH / 2));
-                    const int y = ty0 / 2 + r, x = tx0 / 2 + 8 * kk, co = co0 + col;
-                    if (e < PP && co < cout && y < pool.H && x < pool.W) {
-                        const TO *r0 = &os[col * L::OS + (2 * r) * TW + 16 * kk], *r1 = r0 + TW;
-                        uint32_t w4[4];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const float a0 = 0.25f * ((tof(r0[4 * j]) + tof(r0[4 * j + 1])) +
-                                                      (tof(r1[4 * j]) + tof(r1[4 * j + 1])));
-                            const float a1 = 0.25f * ((tof(r0[4 * j + 2]) + tof(r0[4 * j + 3])) +
-                                                      (tof(r1[4 * j + 2]) + tof(r1[4 * j + 3])));
-                            w4[j] = (uint32_t)__builtin_bit_cast(unsigned short, fromf<TO>(a0)) |
-                                    (uint32_t)__builtin_bit_cast(unsigned short, fromf<TO>(a1)) << 16;
-                        }
-                        *reinterpret_cast<uint4 *>(po + (uint32_t)co * HWo + (uint32_t)(y * pool.W + x)) =
-                            make_uint4(w4[0], w4[1], w4[2], w4[3]);
-                    }
-                }
-            }
-        }
+        conv_tile_out<TO, CO, MH, TW, NT, L::OS>(os, yo, pool, up, n, cout, co0, H, W, tx0, ty0, tid);
     } else {
 #pragma unroll
         for (int m = 0; m < NM; ++m)
@@ -1007,6 +1046,202 @@ __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, con
                     yo[(size_t)co * H * W + (size_t)y * W + x] = fromf<TO>(v);
                 }
             }
+    }
+}
+
+// The same product for launches too small to fill the chip with 8 x 32 pixel
+// tiles: a workgroup of four waves computes 2 x 32 pixels of 16 output channels,
+// wave w the 16 pixels w.  All cin input channels of its 4 x 34 pixels are
+// staged at once with all the weights (one wait for memory, one barrier).
+// Products and sums are those of k_conv3x3_mfma in its order, so the
+// results are its bits.  Bound by the latency of the launch, of that one wait
+// and of the chain of 9 cin / 32 products: 4 to 10 us a layer of one 64 x 256
+// sample (channels 32, 64, 128, 128), where k_conv3x3_mfma, with 4 to 64
+// workgroups and a wait per 32 channels, took 7 to 26.
+// NB (1 or 2): 128-channel blocks of the staged input (cin <= 128 NB).
+constexpr int SH = 2, STW = 32, SCO = 16;
+constexpr int small_lds(int cin) { return ((SH + 2) * (STW + 2) + 9 * SCO) * ((cin + 31) / 32 * 32 + 8) * 2; }
+
+template <class TO, int NB, bool VEC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) k_conv3x3_small(View in, const __bf16 *__restrict__ wp,
+                                                       const float *__restrict__ bias, View out, View pool, View up,
+                                                       int cin, int cout, int cin_pad, int relu) {
+    constexpr int ROWS = SH + 2, COLS = STW + 2, OS = SH * STW + 16 / (int)sizeof(TO);
+    extern __shared__ __attribute__((aligned(16))) char small_smem[];
+    __bf16 *xs = reinterpret_cast<__bf16 *>(small_smem);
+    const int H = in.H, W = in.W;
+    int bxy;
+    {
+        const int nb = gridDim.x * gridDim.y, b = blockIdx.x + gridDim.x * blockIdx.y;
+        const int full = nb / 8 * 8;
+        bxy = b < full ? (b % 8) * (full / 8) + b / 8 : b;
+    }
+    const int bx = bxy % gridDim.x, by = bxy / gridDim.x;
+    const int tiles_x = (W + STW - 1) / STW;
+    const int tx0 = (bx % tiles_x) * STW, ty0 = (bx / tiles_x) * SH;
+    const int ncob = (cout + SCO - 1) / SCO;
+    const int n = by / ncob, co0 = (by % ncob) * SCO;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lr = lane & 15, lk = (lane >> 4) * 8;
+    const int nch = (cin + MCI - 1) / MCI, ps = nch * MCI + 8;      // staged channels per pixel, with padding
+    const __bf16 *__restrict__ xin = static_cast<const __bf16 *>(in.p) + (size_t)n * in.bs;
+    const uint32_t HW = (uint32_t)(H * W);
+
+    __bf16 *ws = xs + ROWS * COLS * ps;                             // [tap][co][ci]
+    const int wco = tid >> 4;
+    bf16x8 w0[9], w1[9];                                            // weights of 128 channels each
+    auto load_w = [&](bf16x8 (&w)[9], int k) {
+        const int c = min(8 * ((tid & 15) + 16 * k), cin_pad - 8);
+        const __bf16 *__restrict__ q = wp + (size_t)min(co0 + wco, cout - 1) * cin_pad + c;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) w[t] = *reinterpret_cast<const bf16x8 *>(q + (size_t)t * cout * cin_pad);
+    };
+    auto store_w = [&](const bf16x8 (&w)[9], int k) {
+        const int c8 = (tid & 15) + 16 * k;
+        if (c8 < 4 * nch) {
+#pragma unroll
+            for (int t = 0; t < 9; ++t) *reinterpret_cast<bf16x8 *>(&ws[(t * SCO + wco) * ps + 8 * c8]) = w[t];
+        }
+    };
+    load_w(w0, 0);
+    if constexpr (NB > 1) load_w(w1, 1);
+    float bv[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int co = co0 + (lane >> 4) * 4 + r;
+        bv[r] = (bias != nullptr && co < cout) ? bias[co] : 0.f;
+    }
+
+    // staging as in ConvStage: tasks of 8 channels x 8 pixels of a row (64 per
+    // chunk) and of 8 channels x 1 halo pixel (32 per chunk)
+    auto wrap = [&](int x) {
+        if (x < 0) x += W;
+        if (x >= W) x -= W;
+        if (x >= W) x %= W;
+        return x;
+    };
+    constexpr int XT = VEC ? 1 : (ROWS * COLS * 16 * NB + 255) / 256;   // !VEC: tasks of 8 channels x 1 pixel
+    const int xtasks = ROWS * COLS * 4 * nch;
+    uint4 v[VEC ? NB : 1][8];
+    uint32_t hv[8];
+    bf16x8 xv[XT];
+    uint32_t vmask[NB], hmask;
+    if constexpr (VEC) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const int e = tid + 256 * k, g = e % 4, r = (e / 4) % ROWS, c8 = e / (4 * ROWS);
+            const int y = ty0 - 1 + r, x = wrap(tx0 + 8 * g);
+            const bool oky = y >= 0 && y < H;
+            const uint32_t pix = (uint32_t)(min(max(y, 0), H - 1) * W + x);
+            vmask[k] = 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int c = 8 * c8 + j;
+                v[k][j] = *reinterpret_cast<const uint4 *>(xin + (uint32_t)min(c, cin - 1) * HW + pix);
+                vmask[k] |= (oky && c < cin ? 1u : 0u) << j;
+            }
+        }
+        {
+            const int h = tid, side = h % 2, r = (h / 2) % ROWS, c8 = h / (2 * ROWS);
+            const int y = ty0 - 1 + r, x = wrap(side ? tx0 + STW : tx0 - 1);
+            const bool oky = y >= 0 && y < H;
+            const uint32_t pix = (uint32_t)(min(max(y, 0), H - 1) * W + x);
+            const unsigned short *__restrict__ xs16 = reinterpret_cast<const unsigned short *>(xin);
+            hmask = 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int c = 8 * c8 + j;
+                hv[j] = xs16[(uint32_t)min(c, cin - 1) * HW + pix];
+                hmask |= (oky && c < cin ? 1u : 0u) << j;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < XT; ++k) {
+            const int e = min(tid + 256 * k, xtasks - 1);
+            const int q = e % COLS, r = (e / COLS) % ROWS, c8 = e / (ROWS * COLS);
+            const uint32_t pix = (uint32_t)(min(max(ty0 - 1 + r, 0), H - 1) * W + wrap(tx0 - 1 + q));
+            if (256 * k < xtasks) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) xv[k][j] = xin[(uint32_t)min(8 * c8 + j, cin - 1) * HW + pix];
+            }
+        }
+    }
+    if constexpr (VEC) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const int e = tid + 256 * k, g = e % 4, r = (e / 4) % ROWS, c8 = e / (4 * ROWS);
+            if (c8 < 4 * nch) {
+                uint4 w[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) w[j] = (vmask[k] >> j & 1u) ? v[k][j] : make_uint4(0u, 0u, 0u, 0u);
+                const uint32_t *u = reinterpret_cast<const uint32_t *>(w);
+#pragma unroll
+                for (int p = 0; p < 8; ++p) {
+                    const uint32_t sel = (p & 1) ? 0x07060302u : 0x05040100u;
+                    const int d = p >> 1;
+                    uint4 o;
+                    o.x = __builtin_amdgcn_perm(u[4 * 1 + d], u[4 * 0 + d], sel);
+                    o.y = __builtin_amdgcn_perm(u[4 * 3 + d], u[4 * 2 + d], sel);
+                    o.z = __builtin_amdgcn_perm(u[4 * 5 + d], u[4 * 4 + d], sel);
+                    o.w = __builtin_amdgcn_perm(u[4 * 7 + d], u[4 * 6 + d], sel);
+                    *reinterpret_cast<uint4 *>(&xs[(r * COLS + 1 + 8 * g + p) * ps + 8 * c8]) = o;
+                }
+            }
+        }
+        {
+            const int h = tid, side = h % 2, r = (h / 2) % ROWS, c8 = h / (2 * ROWS);
+            if (c8 < 4 * nch) {
+                uint32_t hz[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) hz[j] = (hmask >> j & 1u) ? hv[j] & 0xffffu : 0u;
+                *reinterpret_cast<uint4 *>(&xs[(r * COLS + (side ? STW + 1 : 0)) * ps + 8 * c8]) =
+                    make_uint4(hz[0] | hz[1] << 16, hz[2] | hz[3] << 16, hz[4] | hz[5] << 16, hz[6] | hz[7] << 16);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < XT; ++k) {
+            const int e = tid + 256 * k;
+            const int q = e % COLS, r = (e / COLS) % ROWS, c8 = e / (ROWS * COLS);
+            const int y = ty0 - 1 + r;
+            if (e < xtasks) {
+                bf16x8 o = xv[k];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (y < 0 || y >= H || 8 * c8 + j >= cin) o[j] = (__bf16)0.f;
+                *reinterpret_cast<bf16x8 *>(&xs[(r * COLS + q) * ps + 8 * c8]) = o;
+            }
+        }
+    }
+    store_w(w0, 0);
+    if constexpr (NB > 1) store_w(w1, 1);
+    __syncthreads();
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const int pr = wave >> 1, pc = (wave & 1) * 16 + lr;
+    for (int ch = 0; ch < nch; ++ch) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&ws[(t * SCO + lr) * ps + ch * MCI + lk]);
+            const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&xs[((pr + t / 3) * COLS + pc + t % 3) * ps + ch * MCI + lk]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+        }
+    }
+    TO *__restrict__ yo = static_cast<TO *>(out.p) + (size_t)n * out.bs;
+    TO *os = reinterpret_cast<TO *>(small_smem);
+    if constexpr (VEC) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int c = (lane >> 4) * 4 + r;
+        float o = acc[r] + bv[r];
+        if (relu) o = fmaxf(o, 0.f);
+        if constexpr (VEC) os[c * OS + pr * STW + pc] = fromf<TO>(o);
+        else if (co0 + c < cout && ty0 + pr < H && tx0 + pc < W)
+            yo[(uint32_t)(co0 + c) * HW + (uint32_t)((ty0 + pr) * W + tx0 + pc)] = fromf<TO>(o);
+    }
+    if constexpr (VEC) {
+        __syncthreads();
+        conv_tile_out<TO, SCO, SH, STW, 256, OS>(os, yo, pool, up, n, cout, co0, H, W, tx0, ty0, tid);
     }
 }
 
@@ -1267,6 +1502,25 @@ hipError_t launch_conv3x3_mfma_t(const View &in, const __bf16 *wp, const float *
     return hipGetLastError();
 }
 
+// k_conv3x3_small where k_conv3x3_mfma would run at most 64 workgroups of 32
+// channels (a quarter of the CUs) and its channels fit two staging blocks.
+// Forward pass at 64 x 256, us with limits of 0, 64, 128 and 256 workgroups: 1
+// sample 184, 91, 95, 102; 4 samples 190, 144, 150, (above 150); 8 samples 220,
+// 202, 203, (above 203); 1 sample of 200 x 200 (plain staging) 177, 144.
+constexpr long long SMALL_WGS = 64;
+template <class TO, int NB>
+hipError_t launch_conv3x3_small(const View &in, const __bf16 *wp, const float *bias, const View &out, int N,
+                                int cin, int cout, int cin_pad, bool relu, bool vec, const View &pool,
+                                const View &up, hipStream_t s) {
+    const dim3 grid(((in.W + STW - 1) / STW) * ((in.H + SH - 1) / SH), N * ((cout + SCO - 1) / SCO));
+    const int r = relu ? 1 : 0;
+    if (vec)
+        k_conv3x3_small<TO, NB, true><<<grid, 256, small_lds(cin), s>>>(in, wp, bias, out, pool, up, cin, cout, cin_pad, r);
+    else
+        k_conv3x3_small<TO, NB, false><<<grid, 256, small_lds(cin), s>>>(in, wp, bias, out, pool, up, cin, cout, cin_pad, r);
+    return hipGetLastError();
+}
+
 // pool, up (may be NULL): the 2 x 2 pooled and the 2x upsampled output the
 // epilogue also writes when the tile goes through LDS (*pooled, *upped set to
 // whether it did).
@@ -1289,6 +1543,10 @@ hipError_t launch_conv3x3_mfma(const View &in, const __bf16 *wp, const float *bi
                          (uintptr_t)up->p % 16 == 0;
     if (fuse_up) uv = *up;
     if (upped) *upped = fuse_up;
+    const long long wgs32 = (long long)((in.H + MH - 1) / MH) * ((in.W + 31) / 32) * N * ((cout + 31) / 32);
+    if (cin <= 256 && wgs32 <= SMALL_WGS)
+        return cin <= 128 ? launch_conv3x3_small<TO, 1>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s)
+                          : launch_conv3x3_small<TO, 2>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s);
     const long long rows = (in.H + MH - 1) / MH;
     const bool narrow = mfma_narrow(cout) || rows * ((in.W + 31) / 32) * N * ((cout + 63) / 64) < 128;
     const long long wide_wgs = rows * (in.W / 64) * N * (narrow ? (cout + 31) / 32 : (cout + 63) / 64);
@@ -1505,7 +1763,14 @@ hipError_t up_back(const View &dy, const View &dx, int N, int C, hipStream_t s) 
 template <class TA>
 hipError_t conv1x1(const View &in, const float *w, const float *b, int N, int cin, int cout, float *out,
                    hipStream_t s) {
-    k_conv1x1<TA><<<nblk((size_t)N * in.H * in.W), 256, 0, s>>>(in, w, b, N, cin, cout, out);
+    // four pixels per thread from 64 threads per compute unit on, where planes and
+    // rows of pixels are whole aligned groups of four
+    const size_t px = (size_t)N * in.H * in.W;
+    if (px >= (size_t)4 * 256 * 256 && (size_t)in.H * in.W % 4 == 0 && in.bs % 4 == 0 && (uintptr_t)in.p % 16 == 0 &&
+        (uintptr_t)out % 16 == 0)
+        k_conv1x1<TA, 4><<<nblk(px / 4), 256, 0, s>>>(in, w, b, N, cin, cout, out);
+    else
+        k_conv1x1<TA, 1><<<nblk(px), 256, 0, s>>>(in, w, b, N, cin, cout, out);
     return hipGetLastError();
 }
 template hipError_t conv1x1<float>(const View &, const float *, const float *, int, int, int, float *, hipStream_t);

@@ -168,6 +168,23 @@ def test_ragged_widths_match_oracle(net, bf16):
     check_against_fp64(m, bf16, x, t, fluid, specs, theta, samples=6)
 
 
+@pytest.mark.parametrize("H,W,chans", [(64, 64, (32, 64, 128, 128)), (24, 40, (12, 40, 48, 36)), (16, 96, (17, 33, 130, 20)),
+                                       (40, 264, (32, 64, 128, 128))])
+def test_small_batches_are_bitwise_large(net, H, W, chans):
+    """One sample runs the small-launch convolution (2 x 32 pixels of 16
+    channels per workgroup) where 96 samples run the 8-row tiles: the same bits
+    of every output, with cin below, at and above 32 and 128, channel counts that
+    fill no tile, vector and plain staging, and H that ends inside a tile."""
+    x, _, _, _, theta = problem(H, W, 96, chans, 5)
+    big, one = net.Net(H, W, 96, chans=chans), net.Net(H, W, 1, chans=chans)
+    for m in (big, one):
+        m.set_params(theta.astype(np.float32))
+    xd, = to_dev(x)
+    ref = big.forward(xd).cpu().numpy()
+    for i in (0, 1, 50, 95):
+        np.testing.assert_array_equal(one.forward(xd[i:i + 1].contiguous()).cpu().numpy()[0], ref[i])
+
+
 def test_gradient_is_deterministic(net):
     x, t, fluid, specs, theta = problem(n=2, seed=3, **SMALL)
     m = net.Net(SMALL["H"], SMALL["W"], 2, chans=SMALL["chans"])
