@@ -169,7 +169,18 @@ struct lbm_net {
     bool have_grad = false;
     bool packed = false;             // b.wpf holds the current parameters in the forward layout
     bool packed_back = false;        // ... and in the flipped layout of the input gradient
+    // gradients on their way to the host (see fetch): pinned staging memory for
+    // the parameters and the loss, a copy stream, two events per piece
+    float *pin = nullptr;
+    hipStream_t copy = nullptr;
+    std::vector<hipEvent_t> ev;
     std::string err;
+    ~lbm_net() {
+        if (copy) (void)hipStreamSynchronize(copy);
+        for (hipEvent_t e : ev) (void)hipEventDestroy(e);
+        if (copy) (void)hipStreamDestroy(copy);
+        if (pin) (void)hipHostFree(pin);
+    }
 };
 
 namespace {
@@ -412,8 +423,49 @@ lbm_status conv_back(lbm_net *n, int l, const LayerIO &io, int N, const View *po
     return LBM_OK;
 }
 
+// The host copy of a gradient: the backward pass finishes the layers from the
+// last to the first, and a piece of at least FETCH_PIECE finished parameters goes
+// to pinned memory on the copy stream while the pass goes on; the caller's
+// memory is filled from there as the pieces arrive.  (Copied to the caller's
+// pageable memory after the pass, the 1.2 M parameters of the default network
+// took 0.35 ms of a 2.1 ms call, in pieces 0.12.)
+constexpr size_t FETCH_PIECE = size_t(1) << 17;
+struct Fetch {
+    struct Piece { size_t lo, hi; };
+    std::vector<Piece> pieces;
+    size_t lo = 0;                   // parameters from here on are on their way
+};
+
+size_t pin_loss(const lbm_net *n) { return align_up(4 * n->P.nparams, 16); }   // of the loss in pinned memory
+
+lbm_status fetch_init(lbm_net *n) {
+    if (!n->copy) NHIP(n, hipStreamCreateWithFlags(&n->copy, hipStreamNonBlocking));
+    while (n->ev.size() < 2 * (NLAYERS + 1)) {
+        hipEvent_t e;
+        NHIP(n, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        n->ev.push_back(e);
+    }
+    if (!n->pin) NHIP(n, hipHostMalloc((void **)&n->pin, pin_loss(n) + 16, hipHostMallocDefault));
+    return LBM_OK;
+}
+
+// The gradient of the parameters from lo on is enqueued on n->s.
+lbm_status fetch(lbm_net *n, Fetch *f, size_t lo) {
+    if (!f || lo >= f->lo || (lo > 0 && f->lo - lo < FETCH_PIECE)) return LBM_OK;
+    hipEvent_t done = n->ev[2 * f->pieces.size()], here = n->ev[2 * f->pieces.size() + 1];
+    NHIP(n, hipEventRecord(done, n->s));
+    NHIP(n, hipStreamWaitEvent(n->copy, done, 0));
+    NHIP(n, hipMemcpyAsync(n->pin + lo, n->b.grad + lo, 4 * (f->lo - lo), hipMemcpyDeviceToHost, n->copy));
+    if (lo == 0)                     // the last piece takes the loss along
+        NHIP(n, hipMemcpyAsync((char *)n->pin + pin_loss(n), n->b.loss_stats, 16, hipMemcpyDeviceToHost, n->copy));
+    NHIP(n, hipEventRecord(here, n->copy));
+    f->pieces.push_back({lo, f->lo});
+    f->lo = lo;
+    return LBM_OK;
+}
+
 template <class TA>
-lbm_status gradient_t(lbm_net *n, const float *x, const float *tgt, const uint8_t *fluid, int N) {
+lbm_status gradient_t(lbm_net *n, const float *x, const float *tgt, const uint8_t *fluid, int N, Fetch *f = nullptr) {
     const Plan &P = n->P;
     Buffers &b = n->b;
     hipStream_t s = n->s;
@@ -432,6 +484,7 @@ lbm_status gradient_t(lbm_net *n, const float *x, const float *tgt, const uint8_
 #define BACK(L, ...)                                                  \
     do {                                                              \
         if ((st = conv_back<TA>(n, L, io[L], N, ##__VA_ARGS__))) return st; \
+        if ((st = fetch(n, f, P.woff[L]))) return st;                 \
     } while (0)
     BACK(D1B);
     BACK(D1A);
@@ -541,12 +594,30 @@ lbm_status lbm_net_gradient(lbm_net *n, const float *x, const float *t, const ui
     lbm_status st = check_n(n, N);
     if (st) return st;
     if (!x || !t || !fluid) return nfail(n, LBM_EINVAL, "x, t and fluid must not be NULL");
-    st = n->P.bf16 ? gradient_t<__bf16>(n, x, t, fluid, N) : gradient_t<float>(n, x, t, fluid, N);
-    if (st) return st;
+    Fetch f;
+    f.lo = n->P.nparams;
+    // pieces from 1 MB on; below, one copy after the pass is as fast (0.1 M
+    // parameters: 0.03 ms less than in pieces)
+    const bool pieces = grad_host && n->P.nparams >= 2 * FETCH_PIECE && fetch_init(n) == LBM_OK;
+    Fetch *pf = pieces ? &f : nullptr;
+    st = n->P.bf16 ? gradient_t<__bf16>(n, x, t, fluid, N, pf) : gradient_t<float>(n, x, t, fluid, N, pf);
+    if (st) {
+        if (pieces) (void)hipStreamSynchronize(n->copy);
+        return st;
+    }
     double stats[2];
-    NHIP(n, hipMemcpyAsync(stats, n->b.loss_stats, sizeof stats, hipMemcpyDeviceToHost, n->s));
-    if (grad_host)
-        NHIP(n, hipMemcpyAsync(grad_host, n->b.grad, 4 * n->P.nparams, hipMemcpyDeviceToHost, n->s));
+    if (pieces) {
+        for (size_t k = 0; k < f.pieces.size(); ++k) {
+            const Fetch::Piece q = f.pieces[k];
+            NHIP(n, hipEventSynchronize(n->ev[2 * k + 1]));
+            std::memcpy(grad_host + q.lo, n->pin + q.lo, 4 * (q.hi - q.lo));
+        }
+        std::memcpy(stats, (char *)n->pin + pin_loss(n), sizeof stats);
+    } else {
+        NHIP(n, hipMemcpyAsync(stats, n->b.loss_stats, sizeof stats, hipMemcpyDeviceToHost, n->s));
+        if (grad_host)
+            NHIP(n, hipMemcpyAsync(grad_host, n->b.grad, 4 * n->P.nparams, hipMemcpyDeviceToHost, n->s));
+    }
     NHIP(n, hipStreamSynchronize(n->s));
     if (loss) *loss = stats[0];
     return LBM_OK;
