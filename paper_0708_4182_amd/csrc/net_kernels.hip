@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(256) k_conv3x3_dw(View x, const float *__restr
 template <int OB>
 __global__ void __launch_bounds__(256) k_sum_grads(const float *__restrict__ partial, int nchunks, int n,
                                                    float *__restrict__ dw, const float *__restrict__ bpart, int nb,
-                                                   int C, float *__restrict__ db, int wblocks) {
+                                                   int C, float *__restrict__ db, int wblocks, int taps_out) {
     constexpr int G = 256 / OB;
     __shared__ float sh[256];
     const int o = threadIdx.x % OB, g = threadIdx.x / OB;
@@ -233,8 +233,9 @@ __global__ void __launch_bounds__(256) k_sum_grads(const float *__restrict__ par
     if (g != 0 || !live) return;
     float t = sh[o];
     for (int q = 1; q < G; ++q) t += sh[q * OB + o];
+    const int cc = n / 9;
     if (bias) db[i] = t;
-    else dw[i] = t;
+    else dw[taps_out ? (i % cc) * 9 + i / cc : i] = t;
 }
 
 // Sum of v over the workgroup (256 threads), the same tree on every run: a
@@ -518,39 +519,74 @@ __global__ void k_conv1x1_dx(const float *__restrict__ g, const float *__restric
 // 1x1 weight and bias gradients: one workgroup per (o, c) entry, and c = cin
 // for the bias; fixed tree.
 // dW[o][c] = sum of g[n][o](p) x[n][c](p), db[o] = sum of g[n][o](p) (pair c =
-// cin), in two passes with a fixed order: workgroup (pair, b) sums its
-// contiguous share of the N * HW products (fixed tree) into part[pair][b],
-// then k_pair_final adds the BIAS_PARTS shares of each pair in order.
+// cin), in two passes with a fixed order.  Workgroup (b, z, o block) takes share
+// b of the groups of four pixels and the 8 channels from 8 z, four outputs at a
+// time: its wave s holds the 8 x 4 sums of the sub-share s, so that x is read
+// once and g from the caches; lanes and sub-shares are added in a fixed tree
+// into part[pair][b], and k_conv1x1_dw_final adds the BIAS_PARTS shares of each
+// pair in order.
+// Memory-bound: 32 samples of 64 x 256, 32 channels 17 us; one workgroup per
+// pair and share, each reading both planes, took 56.
 constexpr int BIAS_PARTS = 64;
 template <class TA>
-__global__ void __launch_bounds__(256) k_conv1x1_dw_partial(View x, const float *__restrict__ g, int N, int cin,
-                                                            int cout, float *__restrict__ part) {
-    __shared__ float sh[256];
-    const int pair = blockIdx.x, b = blockIdx.y;
-    const int o = pair / (cin + 1), c = pair % (cin + 1);
-    const size_t HW = (size_t)x.H * x.W, total = (size_t)N * HW;
-    const size_t len = (total + BIAS_PARTS - 1) / BIAS_PARTS;
+__global__ void __launch_bounds__(512) k_conv1x1_dw_partial(View x, const float *__restrict__ g, int N, int cin,
+                                                             int cout, float *__restrict__ part) {
+    constexpr int PX = 4, SUB = 8, CQ = 8;
+    typedef TA taN __attribute__((ext_vector_type(PX)));
+    typedef float floatN __attribute__((ext_vector_type(PX)));
+    __shared__ float sh[SUB][4][CQ + 1];              // [sub-share][output][channel | bias]
+    const int b = blockIdx.x, c0 = CQ * blockIdx.y, o0 = 4 * blockIdx.z;
+    const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+    const uint32_t HW = (uint32_t)(x.H * x.W), groups = HW / PX;    // per sample
+    const size_t total = (size_t)N * groups, len = (total + BIAS_PARTS - 1) / BIAS_PARTS;
     const size_t e0 = (size_t)b * len, e1 = min(total, e0 + len);
-    const TA *__restrict__ xp = static_cast<const TA *>(x.p);
-    float s = 0.f;
-    size_t e = e0 + threadIdx.x;
+    float acc[4][CQ + 1] = {};
+    size_t e = e0 + sub * 64 + lane;
     if (e < e1) {
-        // (sample, pixel) of e, advanced by 256 each pass instead of divided
-        uint32_t n = (uint32_t)(e / HW), p = (uint32_t)(e % HW);
-        for (; e < e1; e += 256) {
-            const float gv = g[((size_t)n * cout + o) * HW + p];
-            s += c < cin ? gv * tof(xp[(size_t)n * x.bs + (size_t)c * HW + p]) : gv;
-            p += 256;
-            while (p >= (uint32_t)HW) { p -= (uint32_t)HW; ++n; }
+        // (sample, group) of e, advanced by 64 SUB each pass instead of divided
+        uint32_t n = (uint32_t)(e / groups), p = (uint32_t)(e % groups);
+        for (; e < e1; e += 64 * SUB) {
+            const float *gp = g + ((size_t)n * cout) * HW + (size_t)p * PX;
+            const TA *xp = static_cast<const TA *>(x.p) + (size_t)n * x.bs + (size_t)p * PX;
+            floatN gv[4];
+            taN xv[CQ];
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+                gv[o] = *reinterpret_cast<const floatN *>(gp + (size_t)min(o0 + o, cout - 1) * HW);
+#pragma unroll
+            for (int c = 0; c < CQ; ++c)
+                xv[c] = *reinterpret_cast<const taN *>(xp + (size_t)min(c0 + c, cin - 1) * HW);
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+#pragma unroll
+                for (int k = 0; k < PX; ++k) {
+#pragma unroll
+                    for (int c = 0; c < CQ; ++c) acc[o][c] += gv[o][k] * tof((TA)xv[c][k]);
+                    acc[o][CQ] += gv[o][k];
+                }
+            p += 64 * SUB;
+            while (p >= groups) { p -= groups; ++n; }
         }
     }
-    sh[threadIdx.x] = s;
+#pragma unroll
+    for (int o = 0; o < 4; ++o)
+#pragma unroll
+        for (int c = 0; c <= CQ; ++c) {
+            float v = acc[o][c];
+#pragma unroll
+            for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+            if (lane == 0) sh[sub][o][c] = v;
+        }
     __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (threadIdx.x < k) sh[threadIdx.x] += sh[threadIdx.x + k];
-        __syncthreads();
+    if (threadIdx.x < 4 * (CQ + 1)) {
+        const int c = threadIdx.x % (CQ + 1), o = threadIdx.x / (CQ + 1);
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < SUB; ++k) v += sh[k][o][c];
+        const int ch = c < CQ ? c0 + c : cin;                       // the bias: the first block's
+        if ((c < CQ ? ch < cin : c0 == 0) && o0 + o < cout)
+            part[((size_t)(o0 + o) * (cin + 1) + ch) * BIAS_PARTS + b] = v;
     }
-    if (threadIdx.x == 0) part[(size_t)pair * BIAS_PARTS + b] = sh[0];
 }
 
 __global__ void k_conv1x1_dw_final(const float *__restrict__ part, int cin, int cout, float *__restrict__ dw,
@@ -572,15 +608,33 @@ __global__ void __launch_bounds__(256) k_loss_partial(const float *__restrict__ 
                                                       double *__restrict__ part) {
     __shared__ double sh[2][256];
     double se = 0.0, cnt = 0.0;
-    const size_t total = (size_t)N * HW;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        if (!mask[i]) continue;
-        const size_t n = i / HW, p = i % HW;
-        for (int c = 0; c < C; ++c) {
-            const double d = (double)y[(n * C + c) * HW + p] - (double)t[(n * C + c) * HW + p];
-            se += d * d;
+    const size_t total = (size_t)N * HW, step = (size_t)gridDim.x * 256;
+    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    // (sample, pixel) of i, advanced by step instead of divided; every pixel's
+    // values are loaded, beside the mask, and the solid ones left out
+    const uint32_t sn = (uint32_t)(step / HW), sp = (uint32_t)(step % HW);
+    uint32_t n = (uint32_t)(i / HW), p = (uint32_t)(i % HW);
+#pragma unroll 4
+    for (; i < total; i += step) {
+        const bool fluid = mask[i] != 0;
+        const size_t o = (size_t)n * C * HW + p;
+        for (int c0 = 0; c0 < C; c0 += 4) {
+            float dy[4], dt[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                dy[c] = y[o + (size_t)min(c0 + c, C - 1) * HW];
+                dt[c] = t[o + (size_t)min(c0 + c, C - 1) * HW];
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double d = (double)dy[c] - (double)dt[c];
+                if (fluid && c0 + c < C) se += d * d;
+            }
         }
-        cnt += C;
+        if (fluid) cnt += C;
+        n += sn;
+        p += sp;
+        if (p >= (uint32_t)HW) { p -= (uint32_t)HW; ++n; }
     }
     sh[0][threadIdx.x] = se;
     sh[1][threadIdx.x] = cnt;
@@ -598,12 +652,21 @@ __global__ void __launch_bounds__(256) k_loss_partial(const float *__restrict__ 
     }
 }
 
-__global__ void k_loss_final(const double *__restrict__ part, int n, double *__restrict__ out) {
+// One workgroup of n threads (n = LOSS_BLOCKS): the partials are loaded at once
+// and added in order from LDS (loaded one by one they took 21 us).
+constexpr int LOSS_BLOCKS = 256;
+__global__ void __launch_bounds__(LOSS_BLOCKS) k_loss_final(const double *__restrict__ part,
+                                                            double *__restrict__ out) {
+    __shared__ double sh[2 * LOSS_BLOCKS];
+    sh[2 * threadIdx.x] = part[2 * threadIdx.x];
+    sh[2 * threadIdx.x + 1] = part[2 * threadIdx.x + 1];
+    __syncthreads();
     if (threadIdx.x != 0) return;
     double se = 0.0, cnt = 0.0;
-    for (int k = 0; k < n; ++k) {
-        se += part[2 * k];
-        cnt += part[2 * k + 1];
+#pragma unroll 16
+    for (int k = 0; k < LOSS_BLOCKS; ++k) {
+        se += sh[2 * k];
+        cnt += sh[2 * k + 1];
     }
     out[0] = cnt > 0 ? se / cnt : 0.0;
     out[1] = cnt;
@@ -1255,7 +1318,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
 // operands of the three column shifts come from one 16-byte LDS read of the
 // staged input row plus one neighbouring dword each; each staged row r then
 // serves the dz rows r - dy of the three row shifts.  Partials
-// [chunk][co][ci][tap] are summed in a fixed order by k_sum_grads.
+// [chunk][tap][co][ci] (16 adjacent lanes store 64 contiguous bytes; with the
+// tap innermost the stores took 8 us more a layer) are summed in a fixed
+// order by k_sum_grads.
 constexpr int DM_CO = 32, DM_CI = 32, DM_TR = 4, DM_TW = 32, DM_PX = DM_TR * DM_TW;
 constexpr int DM_DZS = DM_PX + 8;                 // dz channel stride (bf16)
 constexpr int DM_XR = DM_TW + 16;                 // staged x row: 8 | 32 pixels | 8, halo at 7 and 40
@@ -1445,7 +1510,7 @@ __global__ void __launch_bounds__(256) k_conv3x3_dw_mfma(View x, const __bf16 *_
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int co = co0 + wco + (lane >> 4) * 4 + r, ci = ci0 + wci + lr;
-            if (co < cout && ci < cin) partial[(((size_t)chunk * cout + co) * cin + ci) * 9 + t] = acc[t][r];
+            if (co < cout && ci < cin) partial[(((size_t)chunk * 9 + t) * cout + co) * cin + ci] = acc[t][r];
         }
 }
 
@@ -1592,14 +1657,14 @@ bool dw_small(int cin) { return cin <= 4; }
 // Both gradient sums of a layer (k_sum_grads): OB = 64 outputs per workgroup
 // when there are many, else 16 (more threads per output, fewer loads each).
 hipError_t sum_grads(const float *partial, int chunks, int n, float *dw, const float *bpart, int nb, int C,
-                     float *db, hipStream_t s) {
+                     float *db, bool taps_out, hipStream_t s) {
     if (!bpart) C = 0;
     if (n >= 64 * 512) {
         const int wb = (n + 63) / 64;
-        k_sum_grads<64><<<wb + (C + 63) / 64, 256, 0, s>>>(partial, chunks, n, dw, bpart, nb, C, db, wb);
+        k_sum_grads<64><<<wb + (C + 63) / 64, 256, 0, s>>>(partial, chunks, n, dw, bpart, nb, C, db, wb, taps_out);
     } else {
         const int wb = (n + 15) / 16;
-        k_sum_grads<16><<<wb + (C + 15) / 16, 256, 0, s>>>(partial, chunks, n, dw, bpart, nb, C, db, wb);
+        k_sum_grads<16><<<wb + (C + 15) / 16, 256, 0, s>>>(partial, chunks, n, dw, bpart, nb, C, db, wb, taps_out);
     }
     return hipGetLastError();
 }
@@ -1632,7 +1697,7 @@ hipError_t conv3x3_dw(const View &x, const float *dz, int N, int cin, int cout, 
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return sum_grads(partial, chunks, cout * cin * 9, dw, bpart, nb, cout, db, s);
+    return sum_grads(partial, chunks, cout * cin * 9, dw, bpart, nb, cout, db, false, s);
 }
 template hipError_t conv3x3_dw<float>(const View &, const float *, int, int, int, float *, int, float *,
                                       const float *, int, float *, hipStream_t);
@@ -1661,7 +1726,7 @@ hipError_t conv3x3_dw_mfma(const View &x, const __bf16 *dz, int N, int cin, int 
     else k_conv3x3_dw_mfma<false><<<grid, 256, 0, s>>>(x, dz, N, cin, cout, per, partial);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return sum_grads(partial, chunks, cout * cin * 9, dw, bpart, nb, cout, db, s);
+    return sum_grads(partial, chunks, cout * cin * 9, dw, bpart, nb, cout, db, true, s);
 }
 
 namespace {
@@ -1788,7 +1853,9 @@ template <class TA>
 hipError_t conv1x1_dw(const View &x, const float *g, int N, int cin, int cout, float *part, float *dw, float *db,
                       hipStream_t s) {
     const int pairs = cout * (cin + 1);
-    k_conv1x1_dw_partial<TA><<<dim3(pairs, BIAS_PARTS), 256, 0, s>>>(x, g, N, cin, cout, part);
+    const dim3 grid(BIAS_PARTS, (cin + 7) / 8, (cout + 3) / 4);
+    if ((size_t)x.H * x.W % 4 || x.bs % 4 || (uintptr_t)x.p % 16 || (uintptr_t)g % 16) return hipErrorInvalidValue;
+    k_conv1x1_dw_partial<TA><<<grid, 512, 0, s>>>(x, g, N, cin, cout, part);   // planes of a network: multiples of 64
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_conv1x1_dw_final<<<nblk(pairs, 64), 64, 0, s>>>(part, cin, cout, dw, db);
@@ -1799,7 +1866,6 @@ template hipError_t conv1x1_dw<float>(const View &, const float *, int, int, int
 template hipError_t conv1x1_dw<__bf16>(const View &, const float *, int, int, int, float *, float *, float *,
                                        hipStream_t);
 
-constexpr int LOSS_BLOCKS = 256;
 int loss_blocks() { return LOSS_BLOCKS; }
 
 hipError_t loss_and_grad(const float *y, const float *t, const uint8_t *mask, int N, int C, int HW, double *part,
@@ -1807,7 +1873,7 @@ hipError_t loss_and_grad(const float *y, const float *t, const uint8_t *mask, in
     k_loss_partial<<<LOSS_BLOCKS, 256, 0, s>>>(y, t, mask, N, C, HW, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_loss_final<<<1, 64, 0, s>>>(part, LOSS_BLOCKS, stats);
+    k_loss_final<<<1, LOSS_BLOCKS, 0, s>>>(part, stats);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (g) k_loss_grad<<<nblk((size_t)N * C * HW), 256, 0, s>>>(y, t, mask, N, C, HW, stats, g);
     return hipGetLastError();
