@@ -710,12 +710,16 @@ __global__ void k_zero(float *__restrict__ p, size_t n) {
 // A workgroup (4 waves) computes an 8 x 32 pixel tile for 64 output channels;
 // wave w owns pixel rows 2w and 2w + 1 (four 16-pixel N tiles) and all four
 // 16-channel M tiles.  Input channels are staged 32 at a time through LDS
-// channel-last ([y][x][ci], 40 bf16 per pixel so that the 16-byte fragment
-// reads of 16 consecutive pixels fall in distinct banks), with the one-pixel
-// halo (periodic x, zero y); the packed weights ([t][co][ci], see
-// k_pack_all) likewise.
+// channel-last ([y][x][ci], 32 bf16 per pixel), with the one-pixel halo
+// (periodic x, zero y); the packed weights ([t][co][ci], see k_pack_all)
+// likewise.  The four 8-channel pieces of a pixel or weight row are swizzled by
+// stage_at() so that the fragment reads have no bank conflicts: a 16-byte read
+// of a wave takes 4 cycles of the LDS so, and 8 with rows padded to 40, 56 or 72
+// (measured; 48 and 80 are free of conflicts too, and larger).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-constexpr int MH = 8, MCI = 32, MPS = 40;
+constexpr int MH = 8, MCI = 32;
+// bf16 offset of the 8 channels 8 c8 .. (c8 in 0 .. 3) of staged row (pixel or weight row) i.
+__device__ __forceinline__ int stage_at(int i, int c8) { return i * MCI + ((c8 ^ (i >> 1)) & 3) * 8; }
 
 // Packed bf16 weights of every 3x3 matrix-core layer in one launch (workgroup
 // row y packs job y).  Forward layout Wp[t][co][ci] from W[co][ci][t], ci
@@ -747,8 +751,8 @@ struct ConvTile {
 // Staging of one 32-channel chunk of the input tile (rows ty0 - 1 .. ty0 + MH,
 // columns tx0 - 1 .. tx0 + TW, periodic in x, zero outside the rows and
 // channels) and of its packed weights, in two halves: load() issues the
-// global loads into registers, store() writes them to LDS (channel-last,
-// MPS bf16 per pixel).  The loads of chunk k + 1 are issued before the
+// global loads into registers, store() writes them to LDS (channel-last, see
+// stage_at).  The loads of chunk k + 1 are issued before the
 // products of chunk k, so they are in flight while the matrix cores work.
 //
 // VEC (rows of whole 8-pixel groups: W % 8 == 0, 16-byte aligned planes): a
@@ -793,7 +797,7 @@ struct ConvStage {
         const uint32_t HW = (uint32_t)(H * W);
         if constexpr (VEC) {
             if (tid < VIN) {
-                const int g = tid % (TW / 8), r = (tid / (TW / 8)) % (MH + 2), c8 = tid / ((TW / 8) * (MH + 2));
+                const int c8 = tid % 4, g = tid / 4 % (TW / 8), r = tid / (4 * (TW / 8));
                 const int y = ty0 - 1 + r;
                 const int x = wrap(tx0 + 8 * g, W);
                 const bool oky = y >= 0 && y < H;
@@ -808,7 +812,7 @@ struct ConvStage {
                 }
             } else if (tid < VIN + VHALO) {
                 const int h = tid - VIN;
-                const int side = h % 2, r = (h / 2) % (MH + 2), c8 = h / (2 * (MH + 2));
+                const int c8 = h % 4, side = h / 4 % 2, r = h / 8;
                 const int y = ty0 - 1 + r;
                 const int x = wrap(side ? tx0 + TW : tx0 - 1, W);
                 const bool oky = y >= 0 && y < H;
@@ -854,7 +858,7 @@ struct ConvStage {
     __device__ __forceinline__ void store(__bf16 *xs, __bf16 *ws, int tid) const {
         if constexpr (VEC) {
             if (tid < VIN) {
-                const int g = tid % (TW / 8), r = (tid / (TW / 8)) % (MH + 2), c8 = tid / ((TW / 8) * (MH + 2));
+                const int c8 = tid % 4, g = tid / 4 % (TW / 8), r = tid / (4 * (TW / 8));
                 uint4 w[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) w[j] = (vmask >> j & 1u) ? v[j] : make_uint4(0u, 0u, 0u, 0u);
@@ -871,16 +875,16 @@ struct ConvStage {
                     o.y = __builtin_amdgcn_perm(u[4 * 3 + d], u[4 * 2 + d], sel);
                     o.z = __builtin_amdgcn_perm(u[4 * 5 + d], u[4 * 4 + d], sel);
                     o.w = __builtin_amdgcn_perm(u[4 * 7 + d], u[4 * 6 + d], sel);
-                    *reinterpret_cast<uint4 *>(&xs[(r * (TW + 2) + 1 + 8 * g + p) * MPS + 8 * c8]) = o;
+                    *reinterpret_cast<uint4 *>(&xs[stage_at(r * (TW + 2) + 1 + 8 * g + p, c8)]) = o;
                 }
             } else if (tid < VIN + VHALO) {
                 const int h = tid - VIN;
-                const int side = h % 2, r = (h / 2) % (MH + 2), c8 = h / (2 * (MH + 2));
+                const int c8 = h % 4, side = h / 4 % 2, r = h / 8;
                 const int q = side ? TW + 1 : 0;
                 uint32_t hz[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) hz[j] = (vmask >> j & 1u) ? hv[j] & 0xffffu : 0u;
-                *reinterpret_cast<uint4 *>(&xs[(r * (TW + 2) + q) * MPS + 8 * c8]) =
+                *reinterpret_cast<uint4 *>(&xs[stage_at(r * (TW + 2) + q, c8)]) =
                     make_uint4(hz[0] | hz[1] << 16, hz[2] | hz[3] << 16, hz[4] | hz[5] << 16, hz[6] | hz[7] << 16);
             }
         } else {
@@ -893,7 +897,7 @@ struct ConvStage {
 #pragma unroll
                     for (int j = 0; j < 8; ++j)
                         if (!(xmask[k] >> j & 1u)) o[j] = (__bf16)0.f;
-                    *reinterpret_cast<bf16x8 *>(&xs[(r * (TW + 2) + q) * MPS + 8 * c8]) = o;
+                    *reinterpret_cast<bf16x8 *>(&xs[stage_at(r * (TW + 2) + q, c8)]) = o;
                 }
             }
         }
@@ -902,7 +906,7 @@ struct ConvStage {
             const int e = tid + NT * k;
             if (e < WTASKS) {
                 const int c8 = e % (MCI / 8), co = (e / (MCI / 8)) % CO, t = e / ((MCI / 8) * CO);
-                *reinterpret_cast<uint4 *>(&ws[(t * CO + co) * MPS + 8 * c8]) =
+                *reinterpret_cast<uint4 *>(&ws[stage_at(t * CO + co, c8)]) =
                     (wmask >> k & 1u) ? wv[k] : make_uint4(0u, 0u, 0u, 0u);
             }
         }
@@ -915,7 +919,7 @@ struct ConvStage {
 template <class TO, int NM, int TWD>
 struct ConvLds {
     static constexpr int CO = 16 * NM, TW = TWD;
-    static constexpr int XS = (MH + 2) * (TW + 2) * MPS, WS = 9 * CO * MPS;   // bf16
+    static constexpr int XS = (MH + 2) * (TW + 2) * MCI, WS = 9 * CO * MCI;   // bf16
     static constexpr int OS = MH * TW + 16 / (int)sizeof(TO);                 // output row stride
     static constexpr int IN_BYTES = 2 * (XS + WS), OUT_BYTES = CO * OS * (int)sizeof(TO);
     static constexpr int BYTES = IN_BYTES > OUT_BYTES ? IN_BYTES : OUT_BYTES;
@@ -1029,7 +1033,7 @@ __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, con
     const int ncob = (cout + CO - 1) / CO;
     const int n = by / ncob, co0 = (by % ncob) * CO;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lk = (lane >> 4) * 8;
+    const int lr = lane & 15, wlane = stage_at(lr, lane >> 4);
     const __bf16 *__restrict__ xin = static_cast<const __bf16 *>(in.p) + (size_t)n * in.bs;
     // The lane's biases, read before the channel loop: loaded in the epilogue
     // they would put a wait for memory (which on this architecture also waits
@@ -1056,19 +1060,50 @@ __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, con
         st.store(xs, ws, tid);
         __syncthreads();
         if (ci0 + MCI < cin) st.load(xin, wp, H, W, tx0, ty0, ci0 + MCI, cin, cout, co0, cin_pad, tid);
+        // 32 columns, at 2 waves per SIMD and less: the fragments of tap t + 1 are
+        // read while the products of tap t run (16 x 64 128 -> 128, 32 samples
+        // 23.8 -> 20.8 us).  64 columns have no registers left for that (64
+        // channels: 54 -> 60 us with scratch, 32: 28 -> 30).
+        if constexpr (TWD == 32) {
+                bf16x8 a[2][NM], b[2][4];
+            auto frags = [&](int t, bf16x8 (&fa)[NM], bf16x8 (&fb)[4]) {
+                const int dy = t / 3, dx = t % 3;
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+                    fa[m] = *reinterpret_cast<const bf16x8 *>(&ws[(t * CO + 16 * m) * MCI + wlane]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int pr = T::RPW * wave + q / T::QR, pc = (q % T::QR) * 16 + lr;
+                    fb[q] = *reinterpret_cast<const bf16x8 *>(&xs[stage_at((pr + dy) * (TW + 2) + pc + dx, lane >> 4)]);
+                }
+            };
+            frags(0, a[0], b[0]);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                if (t < 8) frags(t + 1, a[(t + 1) & 1], b[(t + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int m = 0; m < NM; ++m)
+                        acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t & 1][m], b[t & 1][q], acc[m][q], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
 #pragma unroll 1
-        for (int t = 0; t < 9; ++t) {
-            const int dy = t / 3, dx = t % 3;
-            bf16x8 a[NM];
+            for (int t = 0; t < 9; ++t) {
+                const int dy = t / 3, dx = t % 3;
+                bf16x8 a[NM];
 #pragma unroll
-            for (int m = 0; m < NM; ++m)
-                a[m] = *reinterpret_cast<const bf16x8 *>(&ws[(t * CO + 16 * m + lr) * MPS + lk]);
+                for (int m = 0; m < NM; ++m)
+                    a[m] = *reinterpret_cast<const bf16x8 *>(&ws[(t * CO + 16 * m) * MCI + wlane]);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int pr = T::RPW * wave + q / T::QR, pc = (q % T::QR) * 16 + lr;
-                const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&xs[((pr + dy) * (TW + 2) + pc + dx) * MPS + lk]);
+                for (int q = 0; q < 4; ++q) {
+                    const int pr = T::RPW * wave + q / T::QR, pc = (q % T::QR) * 16 + lr;
+                    const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&xs[stage_at((pr + dy) * (TW + 2) + pc + dx, lane >> 4)]);
 #pragma unroll
-                for (int m = 0; m < NM; ++m) acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][q], 0, 0, 0);
+                    for (int m = 0; m < NM; ++m) acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][q], 0, 0, 0);
+                }
             }
         }
         __syncthreads();
@@ -1322,9 +1357,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
 // tap innermost the stores took 8 us more a layer) are summed in a fixed
 // order by k_sum_grads.
 constexpr int DM_CO = 32, DM_CI = 32, DM_TR = 4, DM_TW = 32, DM_PX = DM_TR * DM_TW;
-constexpr int DM_DZS = DM_PX + 8;                 // dz channel stride (bf16)
+constexpr int DM_DZS = DM_PX + 16;                // dz channel stride (bf16): an odd multiple of 32 bytes,
 constexpr int DM_XR = DM_TW + 16;                 // staged x row: 8 | 32 pixels | 8, halo at 7 and 40
-constexpr int DM_XSC = (DM_TR + 2) * DM_XR + 8;   // x channel stride (bf16)
+                                                  // at which 16-byte reads have no bank conflicts
+constexpr int DM_XSC = (DM_TR + 2) * DM_XR + 16;  // x channel stride (bf16), likewise
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -1551,8 +1587,11 @@ bool mfma_vec_ok(const View &in, const View &out) {
 // Shape of a convolution launch: 64-column tiles (512 threads) where the
 // rows are whole 64-column tiles and that still gives at least 256
 // workgroups, else 32; 32-channel output tiles for at most 32 output
-// channels or where 64-channel tiles would leave more than half of the 256
-// CUs idle.
+// channels or where 32-column, 64-channel tiles would be at most one workgroup
+// per CU, which two of half the channels overlap better (32 samples, us at 64 and
+// 32 channels: 16 x 64 128 -> 128 20.8, 18.9, 256 -> 128 34.4, 31.4; at 64
+// columns 21.5, 37.6; but 32 x 128 64 -> 64, 512 such tiles: 64 channels and
+// columns 20.1, 32 and 32 26.2).
 template <class TO, int NM, int TWD>
 hipError_t launch_conv3x3_mfma_t(const View &in, const __bf16 *wp, const float *bias, const View &out, int N,
                                  int cin, int cout, int cin_pad, bool relu, bool vec, const View &pool,
@@ -1613,9 +1652,10 @@ hipError_t launch_conv3x3_mfma(const View &in, const __bf16 *wp, const float *bi
         return cin <= 128 ? launch_conv3x3_small<TO, 1>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s)
                           : launch_conv3x3_small<TO, 2>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s);
     const long long rows = (in.H + MH - 1) / MH;
-    const bool narrow = mfma_narrow(cout) || rows * ((in.W + 31) / 32) * N * ((cout + 63) / 64) < 128;
+    const bool few = rows * ((in.W + 31) / 32) * N * ((cout + 63) / 64) <= 256;
+    const bool narrow = mfma_narrow(cout) || few;
     const long long wide_wgs = rows * (in.W / 64) * N * (narrow ? (cout + 31) / 32 : (cout + 63) / 64);
-    const bool wide = vec && in.W % 64 == 0 && wide_wgs >= 256;
+    const bool wide = vec && !few && in.W % 64 == 0 && wide_wgs >= 256;
     if (narrow)
         return wide ? launch_conv3x3_mfma_t<TO, 2, 64>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s)
                     : launch_conv3x3_mfma_t<TO, 2, 32>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s);
