@@ -1009,7 +1009,8 @@ __device__ __forceinline__ void conv_tile_out(const TO *os, TO *__restrict__ yo,
 // tile b' = (b mod 8) * (nb / 8) + b / 8 so that each XCD computes a
 // contiguous run of tiles, and the halo rows and the cache lines that
 // neighbouring tiles share, and the weights, stay in its L2.
-template <class TO, int NM, bool VEC, int TWD>
+// PRE: the fragments of the next tap are read during the products of this one.
+template <class TO, int NM, bool VEC, int TWD, bool PRE>
 __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, const __bf16 *__restrict__ wp,
                                                                      const float *__restrict__ bias, View out,
                                                                      View pool, View up, int cin, int cout,
@@ -1060,11 +1061,12 @@ __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, con
         st.store(xs, ws, tid);
         __syncthreads();
         if (ci0 + MCI < cin) st.load(xin, wp, H, W, tx0, ty0, ci0 + MCI, cin, cout, co0, cin_pad, tid);
-        // 32 columns, at 2 waves per SIMD and less: the fragments of tap t + 1 are
-        // read while the products of tap t run (16 x 64 128 -> 128, 32 samples
-        // 23.8 -> 20.8 us).  64 columns have no registers left for that (64
-        // channels: 54 -> 60 us with scratch, 32: 28 -> 30).
-        if constexpr (TWD == 32) {
+        // the lane's pixel of the first 16 of output row rr at a tap (16 pixels on,
+        // the swizzle is the same)
+        auto xrow = [&](int dy, int dx, int rr) {
+            return stage_at((T::RPW * wave + rr + dy) * (TW + 2) + lr + dx, lane >> 4);
+        };
+        if constexpr (PRE) {
                 bf16x8 a[2][NM], b[2][4];
             auto frags = [&](int t, bf16x8 (&fa)[NM], bf16x8 (&fb)[4]) {
                 const int dy = t / 3, dx = t % 3;
@@ -1072,10 +1074,8 @@ __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, con
                 for (int m = 0; m < NM; ++m)
                     fa[m] = *reinterpret_cast<const bf16x8 *>(&ws[(t * CO + 16 * m) * MCI + wlane]);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int pr = T::RPW * wave + q / T::QR, pc = (q % T::QR) * 16 + lr;
-                    fb[q] = *reinterpret_cast<const bf16x8 *>(&xs[stage_at((pr + dy) * (TW + 2) + pc + dx, lane >> 4)]);
-                }
+                for (int q = 0; q < 4; ++q)
+                    fb[q] = *reinterpret_cast<const bf16x8 *>(&xs[xrow(dy, dx, q / T::QR) + (q % T::QR) * 16 * MCI]);
             };
             frags(0, a[0], b[0]);
 #pragma unroll
@@ -1099,8 +1099,7 @@ __global__ void __launch_bounds__(ConvTile<TWD>::NT) k_conv3x3_mfma(View in, con
                     a[m] = *reinterpret_cast<const bf16x8 *>(&ws[(t * CO + 16 * m) * MCI + wlane]);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int pr = T::RPW * wave + q / T::QR, pc = (q % T::QR) * 16 + lr;
-                    const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&xs[stage_at((pr + dy) * (TW + 2) + pc + dx, lane >> 4)]);
+                    const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&xs[xrow(dy, dx, q / T::QR) + (q % T::QR) * 16 * MCI]);
 #pragma unroll
                     for (int m = 0; m < NM; ++m) acc[m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc[m][q], 0, 0, 0);
                 }
@@ -1348,7 +1347,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
 // x[ci](p + (dy - 1, dx - 1)), a product with K = pixels, where dz is the layer
 // gradient rounded to bf16 by k_relu_mask.  A workgroup owns 32
 // output x 32 input channels (a 2 x 2 grid of waves, 16 x 16 each, all nine
-// taps in 36 accumulation registers) and walks a chunk of 4 x 32 pixel tiles.
+// taps in 36 accumulation registers) and walks a chunk of 4 x 64 (or 32) pixel tiles.
 // The lane's eight K values are eight consecutive pixels of one row, so the
 // operands of the three column shifts come from one 16-byte LDS read of the
 // staged input row plus one neighbouring dword each; each staged row r then
@@ -1356,15 +1355,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))
 // [chunk][tap][co][ci] (16 adjacent lanes store 64 contiguous bytes; with the
 // tap innermost the stores took 8 us more a layer) are summed in a fixed
 // order by k_sum_grads.
-constexpr int DM_CO = 32, DM_CI = 32, DM_TR = 4, DM_TW = 32, DM_PX = DM_TR * DM_TW;
-constexpr int DM_DZS = DM_PX + 16;                // dz channel stride (bf16): an odd multiple of 32 bytes,
-constexpr int DM_XR = DM_TW + 16;                 // staged x row: 8 | 32 pixels | 8, halo at 7 and 40
-                                                  // at which 16-byte reads have no bank conflicts
-constexpr int DM_XSC = (DM_TR + 2) * DM_XR + 16;  // x channel stride (bf16), likewise
+constexpr int DM_CO = 32, DM_CI = 32, DM_TR = 4;
+// A tile of DM_TR rows x TWD columns in LDS (strides in bf16).  16-byte reads at
+// channel strides that are odd multiples of 32 bytes have no bank conflicts.
+template <int TWD>
+struct DwTile {
+    static constexpr int PX = DM_TR * TWD;
+    static constexpr int DZS = PX + 16;                    // dz channel stride
+    static constexpr int XR = TWD + 16;                    // x row: 8 | TWD pixels | 8, halo at 7 and TWD + 8
+    static constexpr int XSC = (DM_TR + 2) * XR + 16;      // x channel stride
+};
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-// x column tx0 + c (c in [-1, 32]) as the staged tile holds it: periodic at
+// x column tx0 + c (c in [-1, TWD]) as the staged tile holds it: periodic at
 // both ends of the row; columns more than one past the last one feed no
 // output pixel and hold zero (-1 returned).
 __device__ __forceinline__ int dw_col(int tx0, int c, int W) {
@@ -1376,132 +1380,188 @@ __device__ __forceinline__ int dw_col(int tx0, int c, int W) {
 
 // Staging of one tile: each thread's share of the dz rows, the x rows and the
 // x halo columns, loaded into registers in one batch (one wait for memory per
-// tile) and written to LDS afterwards.  VEC: whole, aligned 32-pixel rows move
-// as 16-byte loads; otherwise one value per load.
-template <bool VEC>
+// tile) and written to LDS afterwards.
+//
+// VEC (whole, aligned rows of tiles): 16-byte buffer loads.  The offset of each
+// task in its tile is worked out once; a tile adds its own, and rows and
+// channels that do not exist get an offset past the buffer, which reads as zero.
+template <bool VEC, int TWD>
 struct DwStage {
-    static constexpr int DZ_T = VEC ? (DM_CO * DM_TR * (DM_TW / 8) + 255) / 256 : (DM_CO * DM_PX + 255) / 256;
-    static constexpr int X_T = VEC ? (DM_CI * (DM_TR + 2) * (DM_TW / 8) + 255) / 256
-                                   : (DM_CI * (DM_TR + 2) * DM_TW + 255) / 256;
-    static constexpr int H_T = (DM_CI * (DM_TR + 2) * 2 + 255) / 256;
-    using V = typename std::conditional<VEC, bf16x8, __bf16>::type;
-    V dzv[DZ_T], xv[X_T];
-    __bf16 hv[H_T];
+    using L = DwTile<TWD>;
+    static constexpr int DZ = DM_CO * DM_TR * (TWD / 8), XN = DM_CI * (DM_TR + 2) * (TWD / 8), HN = DM_CI * (DM_TR + 2) * 2;
+    static constexpr int DZ_T = (DZ + 255) / 256, X_T = (XN + 255) / 256, H_T = (HN + 255) / 256;
+    static constexpr uint32_t NONE = 0xFFFFFFF1u, PAST = 0xFFFFFFF0u;   // NONE is odd: no offset of a task
+    u32x4 dzv[DZ_T], xv[X_T];
+    uint16_t hv[H_T];
+    uint32_t dzo[DZ_T], xo[X_T], ho[H_T];      // bytes from (0, 0) of the tile; NONE: no such channel
+
+    // tile rows of task k
+    __device__ __forceinline__ static int jrow(int e) { return e / (TWD / 8) % DM_TR; }
+    __device__ __forceinline__ static int xrow(int e) { return e / (TWD / 8) % (DM_TR + 2) - 1; }
+    __device__ __forceinline__ static int hrow(int e) { return (e >> 1) % (DM_TR + 2) - 1; }
+
+    __device__ __forceinline__ void init(int H, int W, int cin, int cout, int co0, int ci0, int tid) {
+        const uint32_t HW = (uint32_t)(H * W);
+#pragma unroll
+        for (int k = 0; k < DZ_T; ++k) {
+            const int e = tid + 256 * k, o = co0 + e / (DM_TR * TWD / 8);
+            dzo[k] = e < DZ && o < cout ? 2u * ((uint32_t)o * HW + jrow(e) * W + (e % (TWD / 8)) * 8) : NONE;
+        }
+#pragma unroll
+        for (int k = 0; k < X_T; ++k) {
+            const int e = tid + 256 * k, c = ci0 + e / ((DM_TR + 2) * TWD / 8);
+            xo[k] = e < XN && c < cin ? 2u * ((uint32_t)c * HW + xrow(e) * W + (e % (TWD / 8)) * 8) : NONE;
+        }
+#pragma unroll
+        for (int k = 0; k < H_T; ++k) {
+            const int e = tid + 256 * k, c = ci0 + (e >> 1) / (DM_TR + 2);
+            ho[k] = e < HN && c < cin ? 2u * ((uint32_t)c * HW + hrow(e) * W) : NONE;
+        }
+    }
+
+    __device__ __forceinline__ void load(const View &x, const __bf16 *__restrict__ dz, int cin, int cout, int n,
+                                         int ty0, int tx0, int tid) {
+        const int H = x.H, W = x.W;
+        const uint32_t HW = (uint32_t)(H * W);
+        const auto rx = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<__bf16 *>(static_cast<const __bf16 *>(x.p) + (size_t)n * x.bs), (short)0, (int)(2u * cin * HW), 0x00020000);
+        const auto rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(dz + (size_t)n * cout * HW), (short)0,
+                                                          (int)(2u * cout * HW), 0x00020000);
+        const uint32_t at = 2u * (uint32_t)(ty0 * W + tx0);
+#pragma unroll
+        for (int k = 0; k < DZ_T; ++k) {
+            const bool ok = dzo[k] != NONE && ty0 + jrow(tid + 256 * k) < H;
+            dzv[k] = __builtin_amdgcn_raw_buffer_load_b128(rz, (int)(ok ? dzo[k] + at : PAST), 0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < X_T; ++k) {
+            const bool ok = xo[k] != NONE && (uint32_t)(ty0 + xrow(tid + 256 * k)) < (uint32_t)H;
+            xv[k] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(ok ? xo[k] + at : PAST), 0, 0);
+        }
+        // halo columns -1 and TWD of every staged row, periodic
+        const uint32_t left = 2u * (uint32_t)(ty0 * W + (tx0 == 0 ? W - 1 : tx0 - 1)),
+                       right = 2u * (uint32_t)(ty0 * W + (tx0 + TWD == W ? 0 : tx0 + TWD));
+#pragma unroll
+        for (int k = 0; k < H_T; ++k) {
+            const bool ok = ho[k] != NONE && (uint32_t)(ty0 + hrow(tid + 256 * k)) < (uint32_t)H;
+            hv[k] = __builtin_amdgcn_raw_buffer_load_b16(rx, (int)(ok ? ho[k] + ((tid & 1) ? right : left) : PAST), 0, 0);
+        }
+    }
+
+    __device__ __forceinline__ void store(__bf16 *dzs, __bf16 *xs, int tid) const {
+#pragma unroll
+        for (int k = 0; k < DZ_T; ++k) {
+            const int e = tid + 256 * k;
+            if (e < DZ)
+                *reinterpret_cast<u32x4 *>(&dzs[e / (DM_TR * TWD / 8) * L::DZS + jrow(e) * TWD + (e % (TWD / 8)) * 8]) = dzv[k];
+        }
+#pragma unroll
+        for (int k = 0; k < X_T; ++k) {
+            const int e = tid + 256 * k;
+            if (e < XN)
+                *reinterpret_cast<u32x4 *>(&xs[e / ((DM_TR + 2) * TWD / 8) * L::XSC + (xrow(e) + 1) * L::XR + 8 +
+                                               (e % (TWD / 8)) * 8]) = xv[k];
+        }
+#pragma unroll
+        for (int k = 0; k < H_T; ++k) {
+            const int e = tid + 256 * k;
+            if (e < HN)
+                reinterpret_cast<uint16_t *>(xs)[(e >> 1) / (DM_TR + 2) * L::XSC + (hrow(e) + 1) * L::XR +
+                                                 ((e & 1) ? 8 + TWD : 7)] = hv[k];
+        }
+    }
 };
 
-template <bool VEC>
-__device__ __forceinline__ void dw_load(DwStage<VEC> &st, const View &x, const __bf16 *__restrict__ dz, int cin,
-                                        int cout, int co0, int ci0, int tile, int tiles_x, int tiles_y, int tid) {
-    const int H = x.H, W = x.W;
-    const int n = tile / (tiles_x * tiles_y), rem = tile % (tiles_x * tiles_y);
-    const int ty0 = (rem / tiles_x) * DM_TR, tx0 = (rem % tiles_x) * DM_TW;
-    const __bf16 *__restrict__ xin = static_cast<const __bf16 *>(x.p) + (size_t)n * x.bs;
-    const __bf16 *__restrict__ dzn = dz + (size_t)n * cout * H * W;
-    const __bf16 zero = (__bf16)0.f;
-    if constexpr (VEC) {
-#pragma unroll
-        for (int k = 0; k < DwStage<VEC>::DZ_T; ++k) {
-            const int e = tid + 256 * k;
-            const int q = (e % (DM_TW / 8)) * 8, j = (e / (DM_TW / 8)) % DM_TR, o = e / (DM_TR * DM_TW / 8);
-            const int y = ty0 + j;
-            st.dzv[k] = bf16x8{zero, zero, zero, zero, zero, zero, zero, zero};
-            if (e < DM_CO * DM_TR * (DM_TW / 8) && co0 + o < cout && y < H)
-                st.dzv[k] = *reinterpret_cast<const bf16x8 *>(&dzn[(size_t)(co0 + o) * H * W + (size_t)y * W + tx0 + q]);
-        }
-#pragma unroll
-        for (int k = 0; k < DwStage<VEC>::X_T; ++k) {
-            const int e = tid + 256 * k;
-            const int q = (e % (DM_TW / 8)) * 8, r = (e / (DM_TW / 8)) % (DM_TR + 2), c = e / ((DM_TR + 2) * DM_TW / 8);
-            const int y = ty0 - 1 + r;
-            st.xv[k] = bf16x8{zero, zero, zero, zero, zero, zero, zero, zero};
-            if (e < DM_CI * (DM_TR + 2) * (DM_TW / 8) && ci0 + c < cin && y >= 0 && y < H)
-                st.xv[k] = *reinterpret_cast<const bf16x8 *>(&xin[(size_t)(ci0 + c) * H * W + (size_t)y * W + tx0 + q]);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < DwStage<VEC>::DZ_T; ++k) {
-            const int e = tid + 256 * k;
-            const int o = e / DM_PX, p = e % DM_PX;
-            const int y = ty0 + p / DM_TW, xx = tx0 + p % DM_TW;
-            st.dzv[k] = zero;
-            if (e < DM_CO * DM_PX && co0 + o < cout && y < H && xx < W)
-                st.dzv[k] = dzn[(size_t)(co0 + o) * H * W + (size_t)y * W + xx];
-        }
-#pragma unroll
-        for (int k = 0; k < DwStage<VEC>::X_T; ++k) {
-            const int e = tid + 256 * k;
-            const int q = e % DM_TW, r = (e / DM_TW) % (DM_TR + 2), c = e / ((DM_TR + 2) * DM_TW);
-            const int y = ty0 - 1 + r, col = dw_col(tx0, q, W);
-            st.xv[k] = zero;
-            if (e < DM_CI * (DM_TR + 2) * DM_TW && ci0 + c < cin && y >= 0 && y < H && col >= 0)
-                st.xv[k] = xin[(size_t)(ci0 + c) * H * W + (size_t)y * W + col];
-        }
-    }
-    // halo columns -1 and 32 of every staged row
-#pragma unroll
-    for (int k = 0; k < DwStage<VEC>::H_T; ++k) {
-        const int e = tid + 256 * k;
-        const int side = e & 1, r = (e >> 1) % (DM_TR + 2), c = (e >> 1) / (DM_TR + 2);
-        const int y = ty0 - 1 + r, col = dw_col(tx0, side ? DM_TW : -1, W);
-        st.hv[k] = zero;
-        if (e < DM_CI * (DM_TR + 2) * 2 && ci0 + c < cin && y >= 0 && y < H && col >= 0)
-            st.hv[k] = xin[(size_t)(ci0 + c) * H * W + (size_t)y * W + col];
-    }
-}
+// Any other row length and alignment: one value per load.
+template <int TWD>
+struct DwStage<false, TWD> {
+    using L = DwTile<TWD>;
+    static constexpr int DZ = DM_CO * L::PX, XN = DM_CI * (DM_TR + 2) * TWD, HN = DM_CI * (DM_TR + 2) * 2;
+    static constexpr int DZ_T = (DZ + 255) / 256, X_T = (XN + 255) / 256, H_T = (HN + 255) / 256;
+    __bf16 dzv[DZ_T], xv[X_T], hv[H_T];
+    int co0, ci0;
 
-template <bool VEC>
-__device__ __forceinline__ void dw_store(const DwStage<VEC> &st, __bf16 *dzs, __bf16 *xs, int tid) {
-    if constexpr (VEC) {
+    __device__ __forceinline__ void init(int, int, int, int, int co, int ci, int) { co0 = co, ci0 = ci; }
+    __device__ __forceinline__ void load(const View &x, const __bf16 *__restrict__ dz, int cin, int cout, int n,
+                                         int ty0, int tx0, int tid) {
+        const int H = x.H, W = x.W;
+        const __bf16 *__restrict__ xin = static_cast<const __bf16 *>(x.p) + (size_t)n * x.bs;
+        const __bf16 *__restrict__ dzn = dz + (size_t)n * cout * H * W;
+        const __bf16 zero = (__bf16)0.f;
 #pragma unroll
-        for (int k = 0; k < DwStage<VEC>::DZ_T; ++k) {
+        for (int k = 0; k < DZ_T; ++k) {
             const int e = tid + 256 * k;
-            if (e >= DM_CO * DM_TR * (DM_TW / 8)) continue;
-            const int q = (e % (DM_TW / 8)) * 8, j = (e / (DM_TW / 8)) % DM_TR, o = e / (DM_TR * DM_TW / 8);
-            *reinterpret_cast<bf16x8 *>(&dzs[o * DM_DZS + j * DM_TW + q]) = st.dzv[k];
+            const int o = e / L::PX, p = e % L::PX;
+            const int y = ty0 + p / TWD, xx = tx0 + p % TWD;
+            dzv[k] = zero;
+            if (e < DZ && co0 + o < cout && y < H && xx < W)
+                dzv[k] = dzn[(size_t)(co0 + o) * H * W + (size_t)y * W + xx];
         }
 #pragma unroll
-        for (int k = 0; k < DwStage<VEC>::X_T; ++k) {
+        for (int k = 0; k < X_T; ++k) {
             const int e = tid + 256 * k;
-            if (e >= DM_CI * (DM_TR + 2) * (DM_TW / 8)) continue;
-            const int q = (e % (DM_TW / 8)) * 8, r = (e / (DM_TW / 8)) % (DM_TR + 2), c = e / ((DM_TR + 2) * DM_TW / 8);
-            *reinterpret_cast<bf16x8 *>(&xs[c * DM_XSC + r * DM_XR + 8 + q]) = st.xv[k];
+            const int q = e % TWD, r = (e / TWD) % (DM_TR + 2), c = e / ((DM_TR + 2) * TWD);
+            const int y = ty0 - 1 + r, col = dw_col(tx0, q, W);
+            xv[k] = zero;
+            if (e < XN && ci0 + c < cin && y >= 0 && y < H && col >= 0)
+                xv[k] = xin[(size_t)(ci0 + c) * H * W + (size_t)y * W + col];
         }
-    } else {
+        // halo columns -1 and TWD of every staged row
 #pragma unroll
-        for (int k = 0; k < DwStage<VEC>::DZ_T; ++k) {
+        for (int k = 0; k < H_T; ++k) {
             const int e = tid + 256 * k;
-            if (e >= DM_CO * DM_PX) continue;
-            dzs[(e / DM_PX) * DM_DZS + e % DM_PX] = st.dzv[k];
-        }
-#pragma unroll
-        for (int k = 0; k < DwStage<VEC>::X_T; ++k) {
-            const int e = tid + 256 * k;
-            if (e >= DM_CI * (DM_TR + 2) * DM_TW) continue;
-            const int q = e % DM_TW, r = (e / DM_TW) % (DM_TR + 2), c = e / ((DM_TR + 2) * DM_TW);
-            xs[c * DM_XSC + r * DM_XR + 8 + q] = st.xv[k];
+            const int side = e & 1, r = (e >> 1) % (DM_TR + 2), c = (e >> 1) / (DM_TR + 2);
+            const int y = ty0 - 1 + r, col = dw_col(tx0, side ? TWD : -1, W);
+            hv[k] = zero;
+            if (e < HN && ci0 + c < cin && y >= 0 && y < H && col >= 0)
+                hv[k] = xin[(size_t)(ci0 + c) * H * W + (size_t)y * W + col];
         }
     }
+    __device__ __forceinline__ void store(__bf16 *dzs, __bf16 *xs, int tid) const {
 #pragma unroll
-    for (int k = 0; k < DwStage<VEC>::H_T; ++k) {
-        const int e = tid + 256 * k;
-        if (e >= DM_CI * (DM_TR + 2) * 2) continue;
-        const int side = e & 1, r = (e >> 1) % (DM_TR + 2), c = (e >> 1) / (DM_TR + 2);
-        xs[c * DM_XSC + r * DM_XR + (side ? 8 + DM_TW : 7)] = st.hv[k];
+        for (int k = 0; k < DZ_T; ++k) {
+            const int e = tid + 256 * k;
+            if (e < DZ) dzs[(e / L::PX) * L::DZS + e % L::PX] = dzv[k];
+        }
+#pragma unroll
+        for (int k = 0; k < X_T; ++k) {
+            const int e = tid + 256 * k;
+            const int q = e % TWD, r = (e / TWD) % (DM_TR + 2), c = e / ((DM_TR + 2) * TWD);
+            if (e < XN) xs[c * L::XSC + r * L::XR + 8 + q] = xv[k];
+        }
+#pragma unroll
+        for (int k = 0; k < H_T; ++k) {
+            const int e = tid + 256 * k;
+            const int side = e & 1, r = (e >> 1) % (DM_TR + 2), c = (e >> 1) / (DM_TR + 2);
+            if (e < HN) xs[c * L::XSC + r * L::XR + (side ? 8 + TWD : 7)] = hv[k];
+        }
     }
-}
+};
 
 // The tiles of a chunk are software-pipelined: the next tile's loads are in
-// flight (in registers) while the current tile's products run from LDS.
-template <bool VEC>
+// flight (in registers) while the current tile's products run from LDS.  Bound by
+// memory where the blocks are few (32 -> 32 at 64 x 256: 67 MB in 22 us with the
+// partials) and by the serial work of 2 waves per SIMD where they are many.  The
+// 13 layers of the default network, 32 samples of 64 x 256: 446 us with 32-column
+// tiles, address arithmetic per load and blocks of a chunk on any XCD, 428 with
+// those on one, 391 with 64 columns, 365 with buffer loads.
+template <bool VEC, int TWD>
 __global__ void __launch_bounds__(256) k_conv3x3_dw_mfma(View x, const __bf16 *__restrict__ dz, int N, int cin,
                                                          int cout, int tiles_per_chunk,
                                                          float *__restrict__ partial) {
+    constexpr int DM_TW = TWD, DM_DZS = DwTile<TWD>::DZS, DM_XR = DwTile<TWD>::XR, DM_XSC = DwTile<TWD>::XSC, KH = TWD / 32;
     __shared__ __attribute__((aligned(16))) __bf16 dzs[DM_CO * DM_DZS];
     __shared__ __attribute__((aligned(16))) __bf16 xs[DM_CI * DM_XSC];
     const int H = x.H, W = x.W;
     const int tiles_x = (W + DM_TW - 1) / DM_TW, tiles_y = (H + DM_TR - 1) / DM_TR;
     const int ntiles = N * tiles_x * tiles_y;
-    const int chunk = blockIdx.x, co0 = blockIdx.y * DM_CO, ci0 = blockIdx.z * DM_CI;
+    // Workgroups go round-robin over the 8 XCDs: each XCD gets a contiguous run of
+    // (chunk, co block, ci block), so that the blocks of a chunk read its tiles
+    // from one L2 at about the same time.
+    const int nco = gridDim.y, nci = gridDim.z, nb = gridDim.x * nco * nci;
+    const int b = blockIdx.x + gridDim.x * (blockIdx.y + nco * blockIdx.z), full = nb / 8 * 8;
+    const int at = b < full ? (b % 8) * (full / 8) + b / 8 : b;
+    const int chunk = at / (nco * nci), co0 = at / nci % nco * DM_CO, ci0 = at % nci * DM_CI;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wco = (wave & 1) * 16, wci = (wave >> 1) * 16;
     const int lr = lane & 15, lk = (lane >> 4) * 8;
@@ -1509,19 +1569,29 @@ __global__ void __launch_bounds__(256) k_conv3x3_dw_mfma(View x, const __bf16 *_
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int t_begin = chunk * tiles_per_chunk, t_end = min(ntiles, t_begin + tiles_per_chunk);
-    DwStage<VEC> st;
-    if (t_begin < t_end) dw_load<VEC>(st, x, dz, cin, cout, co0, ci0, t_begin, tiles_x, tiles_y, tid);
+    DwStage<VEC, TWD> st;
+    st.init(H, W, cin, cout, co0, ci0, tid);
+    int n = t_begin / (tiles_x * tiles_y), ty = t_begin % (tiles_x * tiles_y) / tiles_x, tx = t_begin % tiles_x;
+    if (t_begin < t_end) st.load(x, dz, cin, cout, n, ty * DM_TR, tx * TWD, tid);
     for (int tile = t_begin; tile < t_end; ++tile) {
-        dw_store<VEC>(st, dzs, xs, tid);
+        st.store(dzs, xs, tid);
         __syncthreads();
-        if (tile + 1 < t_end) dw_load<VEC>(st, x, dz, cin, cout, co0, ci0, tile + 1, tiles_x, tiles_y, tid);
+        if (tile + 1 < t_end) {
+            if (++tx == tiles_x) {
+                tx = 0;
+                if (++ty == tiles_y) ty = 0, ++n;
+            }
+            st.load(x, dz, cin, cout, n, ty * DM_TR, tx * TWD, tid);
+        }
+#pragma unroll
+      for (int h = 0; h < KH; ++h) {        // 32 pixels of each row
         bf16x8 a[DM_TR];
 #pragma unroll
         for (int j = 0; j < DM_TR; ++j)
-            a[j] = *reinterpret_cast<const bf16x8 *>(&dzs[(wco + lr) * DM_DZS + j * DM_TW + lk]);
+            a[j] = *reinterpret_cast<const bf16x8 *>(&dzs[(wco + lr) * DM_DZS + j * DM_TW + 32 * h + lk]);
 #pragma unroll
         for (int r = 0; r < DM_TR + 2; ++r) {
-            const __bf16 *row = &xs[(wci + lr) * DM_XSC + r * DM_XR + 8 + lk];
+            const __bf16 *row = &xs[(wci + lr) * DM_XSC + r * DM_XR + 8 + 32 * h + lk];
             const u32x4 c = __builtin_bit_cast(u32x4, *reinterpret_cast<const bf16x8 *>(row));
             const uint32_t lw = *reinterpret_cast<const uint32_t *>(row - 2);   // pixels lk - 2, lk - 1
             const uint32_t rw = *reinterpret_cast<const uint32_t *>(row + 8);   // pixels lk + 8, lk + 9
@@ -1539,6 +1609,7 @@ __global__ void __launch_bounds__(256) k_conv3x3_dw_mfma(View x, const __bf16 *_
                     acc[dy * 3 + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j], b[dx], acc[dy * 3 + dx], 0, 0, 0);
             }
         }
+      }
         __syncthreads();
     }
 #pragma unroll
@@ -1587,12 +1658,15 @@ bool mfma_vec_ok(const View &in, const View &out) {
 // Shape of a convolution launch: 64-column tiles (512 threads) where the
 // rows are whole 64-column tiles and that still gives at least 256
 // workgroups, else 32; 32-channel output tiles for at most 32 output
-// channels or where 32-column, 64-channel tiles would be at most one workgroup
-// per CU, which two of half the channels overlap better (32 samples, us at 64 and
-// 32 channels: 16 x 64 128 -> 128 20.8, 18.9, 256 -> 128 34.4, 31.4; at 64
-// columns 21.5, 37.6; but 32 x 128 64 -> 64, 512 such tiles: 64 channels and
-// columns 20.1, 32 and 32 26.2).
-template <class TO, int NM, int TWD>
+// channels or where 64-channel tiles would leave more than half of the 256
+// CUs idle.  With vector staging, 32-channel tiles also where 32-column,
+// 64-channel ones would be at most one workgroup per CU, and then with the
+// fragments read one tap ahead: at 2 waves per SIMD two workgroups overlap each
+// other, and each its own reads (32 samples of 16 x 64, us at 64 channels, 32, 32
+// one tap ahead: 128 -> 128 23.8, 23, 18.9; 256 -> 128 39, 36, 31.4).  Not for
+// more workgroups: 24 samples of 64 x 160, 12 channels, forward 203 -> 215 us;
+// 64-column tiles have no registers for it (64 channels 54 -> 60 us).
+template <class TO, int NM, int TWD, bool PRE = false>
 hipError_t launch_conv3x3_mfma_t(const View &in, const __bf16 *wp, const float *bias, const View &out, int N,
                                  int cin, int cout, int cin_pad, bool relu, bool vec, const View &pool,
                                  const View &up, hipStream_t s) {
@@ -1600,9 +1674,9 @@ hipError_t launch_conv3x3_mfma_t(const View &in, const __bf16 *wp, const float *
     const dim3 grid(tiles, N * ((cout + 16 * NM - 1) / (16 * NM)));
     const int r = relu ? 1 : 0, nt = ConvTile<TWD>::NT;
     if (vec)
-        k_conv3x3_mfma<TO, NM, true, TWD><<<grid, nt, 0, s>>>(in, wp, bias, out, pool, up, cin, cout, cin_pad, r);
-    else
-        k_conv3x3_mfma<TO, NM, false, TWD><<<grid, nt, 0, s>>>(in, wp, bias, out, pool, up, cin, cout, cin_pad, r);
+        k_conv3x3_mfma<TO, NM, true, TWD, PRE><<<grid, nt, 0, s>>>(in, wp, bias, out, pool, up, cin, cout, cin_pad, r);
+    else if constexpr (!PRE)
+        k_conv3x3_mfma<TO, NM, false, TWD, false><<<grid, nt, 0, s>>>(in, wp, bias, out, pool, up, cin, cout, cin_pad, r);
     return hipGetLastError();
 }
 
@@ -1652,10 +1726,12 @@ hipError_t launch_conv3x3_mfma(const View &in, const __bf16 *wp, const float *bi
         return cin <= 128 ? launch_conv3x3_small<TO, 1>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s)
                           : launch_conv3x3_small<TO, 2>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s);
     const long long rows = (in.H + MH - 1) / MH;
-    const bool few = rows * ((in.W + 31) / 32) * N * ((cout + 63) / 64) <= 256;
-    const bool narrow = mfma_narrow(cout) || few;
+    const long long wgs = rows * ((in.W + 31) / 32) * N * ((cout + 63) / 64);
+    if (vec && wgs <= 256)
+        return launch_conv3x3_mfma_t<TO, 2, 32, true>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s);
+    const bool narrow = mfma_narrow(cout) || wgs < 128;
     const long long wide_wgs = rows * (in.W / 64) * N * (narrow ? (cout + 31) / 32 : (cout + 63) / 64);
-    const bool wide = vec && !few && in.W % 64 == 0 && wide_wgs >= 256;
+    const bool wide = vec && in.W % 64 == 0 && wide_wgs >= 256;
     if (narrow)
         return wide ? launch_conv3x3_mfma_t<TO, 2, 64>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s)
                     : launch_conv3x3_mfma_t<TO, 2, 32>(in, wp, bias, out, N, cin, cout, cin_pad, relu, vec, pv, uv, s);
@@ -1744,8 +1820,15 @@ template hipError_t conv3x3_dw<float>(const View &, const float *, int, int, int
 template hipError_t conv3x3_dw<__bf16>(const View &, const float *, int, int, int, float *, int, float *,
                                        const float *, int, float *, hipStream_t);
 
+namespace {
+// Columns of a weight-gradient tile: 64 (whole 128-byte lines) where the rows are
+// whole such tiles, else 32.
+int dw_tile(int W) { return W % 64 == 0 ? 64 : 32; }
+int dw_tiles(int N, int H, int W) { return N * ((W + dw_tile(W) - 1) / dw_tile(W)) * ((H + DM_TR - 1) / DM_TR); }
+}  // namespace
+
 int dw_chunks_mfma(int N, int H, int W, int cin, int cout) {
-    const int ntiles = N * ((W + DM_TW - 1) / DM_TW) * ((H + DM_TR - 1) / DM_TR);
+    const int ntiles = dw_tiles(N, H, W);
     const int blocks = ((cout + DM_CO - 1) / DM_CO) * ((cin + DM_CI - 1) / DM_CI);
     // about 512 workgroups, at least 2 tiles per chunk: fewer chunk partials to
     // sum (training measured 3.75 ms per batch with 1024, 3.56 with 512, 3.74
@@ -1755,15 +1838,21 @@ int dw_chunks_mfma(int N, int H, int W, int cin, int cout) {
 
 hipError_t conv3x3_dw_mfma(const View &x, const __bf16 *dz, int N, int cin, int cout, float *partial, int chunks,
                            float *dw, const float *bpart, int nb, float *db, hipStream_t s) {
-    const int ntiles = N * ((x.W + DM_TW - 1) / DM_TW) * ((x.H + DM_TR - 1) / DM_TR);
-    const int per = (ntiles + chunks - 1) / chunks;
+    const int per = (dw_tiles(N, x.H, x.W) + chunks - 1) / chunks;
     // vector staging: whole tile rows and 16-byte aligned rows of x and dz
     const size_t hw = (size_t)x.H * x.W;
-    const int vec = x.W % DM_TW == 0 && hw % 8 == 0 && x.bs % 8 == 0 && (uintptr_t)x.p % 16 == 0 &&
-                    (uintptr_t)dz % 16 == 0;
+    const bool vec = x.W % 32 == 0 && hw % 8 == 0 && x.bs % 8 == 0 && (uintptr_t)x.p % 16 == 0 &&
+                     (uintptr_t)dz % 16 == 0 && (unsigned long long)std::max(cin, cout) * hw < 0x7FFF0000ull;
     const dim3 grid(chunks, (cout + DM_CO - 1) / DM_CO, (cin + DM_CI - 1) / DM_CI);
-    if (vec) k_conv3x3_dw_mfma<true><<<grid, 256, 0, s>>>(x, dz, N, cin, cout, per, partial);
-    else k_conv3x3_dw_mfma<false><<<grid, 256, 0, s>>>(x, dz, N, cin, cout, per, partial);
+    if (dw_tile(x.W) == 64 && !vec) {
+        k_conv3x3_dw_mfma<false, 64><<<grid, 256, 0, s>>>(x, dz, N, cin, cout, per, partial);
+    } else if (dw_tile(x.W) == 64) {
+        k_conv3x3_dw_mfma<true, 64><<<grid, 256, 0, s>>>(x, dz, N, cin, cout, per, partial);
+    } else if (vec) {
+        k_conv3x3_dw_mfma<true, 32><<<grid, 256, 0, s>>>(x, dz, N, cin, cout, per, partial);
+    } else {
+        k_conv3x3_dw_mfma<false, 32><<<grid, 256, 0, s>>>(x, dz, N, cin, cout, per, partial);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return sum_grads(partial, chunks, cout * cin * 9, dw, bpart, nb, cout, db, true, s);

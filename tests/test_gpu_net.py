@@ -185,6 +185,29 @@ def test_small_batches_are_bitwise_large(net, H, W, chans):
         np.testing.assert_array_equal(one.forward(xd[i:i + 1].contiguous()).cpu().numpy()[0], ref[i])
 
 
+@pytest.mark.parametrize("H,W,n", [(16, 64, 1), (24, 128, 3), (8, 192, 2), (40, 256, 2), (16, 72, 5)])
+def test_gradient_rolls_with_its_inputs(net, H, W, n):
+    """Rows are periodic: inputs rolled by a multiple of 8 pixels (the coarsest
+    level's pixel) give the same stored activations and layer gradients, rolled,
+    so the weight gradient changes only by the order of its FP32 sums (bar
+    1e-5 per block, as for FP32).  64- and 32-column and gathered tiles of the
+    weight gradient, rows of one and several tiles, H within a tile."""
+    chans = (12, 33, 40, 20)
+    x, t, fluid, specs, theta = problem(H, W, n, chans, 11)
+    m = net.Net(H, W, n, chans=chans)
+    m.set_params(theta)
+    loss, g = m.gradient(*to_dev(x, t, fluid))
+    for shift in (8, 24, W // 2 // 8 * 8, W - 8):
+        l2, g2 = m.gradient(*to_dev(*(np.roll(a, shift, axis=-1) for a in (x, t, fluid))))
+        assert abs(l2 - loss) <= 1e-12 * abs(loss)
+        o = 0
+        for _, ci, co, k in specs:
+            for size in (co * ci * k * k, co):
+                a, b = g[o:o + size].astype(np.float64), g2[o:o + size].astype(np.float64)
+                assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(a), (shift, ci, co, size)
+                o += size
+
+
 def test_gradient_is_deterministic(net):
     x, t, fluid, specs, theta = problem(n=2, seed=3, **SMALL)
     m = net.Net(SMALL["H"], SMALL["W"], 2, chans=SMALL["chans"])
