@@ -478,7 +478,7 @@ int strip_columns(const lbm_sim *s, int kernel) {
 int node_rows_for(const lbm_sim *s, int kernel) {
     const int k = steps_per_launch(kernel);
     if ((kernel != LBM_KERNEL_FUSED && kernel != LBM_KERNEL_TWO) ||
-        !lbm::node_fits((int64_t)18 * s->p.nx * s->p.ny * (int64_t)elem_size(s->p.storage), s->rows))
+        !lbm::node_fits(s->p.storage, (int64_t)s->p.nx * s->p.ny, k, s->rows))
         return 0;
     return lbm::node_height(lbm::node_tiles8(s->p.nx, s->p.ny, k), k, s->cus);
 }
@@ -530,6 +530,7 @@ lbm::StepArgs step_args_for(lbm_sim *s, int kernel, int &cache) {
     a.par = s->cur;
     a.acc = s->acc;
     a.node = node;
+    a.cus = s->cus;
     return a;
 }
 

@@ -152,6 +152,7 @@ struct lbm_batch {
     bool tile_auto = true;             // no tile was asked for
     int node1 = 0, nodek = 0;          // rows per workgroup of rectangle launches of one and of kstep steps (0: march)
     int node1_tiles = 0, nodek_tiles = 0;   // their workgroups per channel
+    int node1_wgs = 0, nodek_wgs = 0;       // ... and those with a tile, in all
     int ntiles = 0;
     int kstep = 1;                     // time steps per launch: 1, or 2 / 3 (k_batch_tilesk)
     int kbx = 256;                     // block_x of the multi-step kernel (256 or 512)
@@ -222,22 +223,24 @@ lbm_status upload_tiles(lbm_batch *b) {
     b->host_tiles.clear();
     b->host_tiles_k.clear();
     // rectangle launches, where a single lattice of this size would run them
-    int64_t bytes = 0, tiles8 = 0, tiles8_k = 0;
+    int64_t nodes = 0, tiles8 = 0, tiles8_k = 0;
     for (int i : order) {
-        bytes += (int64_t)18 * b->g[i].nx * b->g[i].ny * (int64_t)elem_size(b->storage);
+        nodes += (int64_t)b->g[i].nx * b->g[i].ny;
         tiles8 += lbm::node_tiles8(b->g[i].nx, b->g[i].ny, 1);
         tiles8_k += lbm::node_tiles8(b->g[i].nx, b->g[i].ny, 2);
     }
-    const bool fits = lbm::node_fits(bytes, b->tile_auto ? 0 : b->tile_rows);
-    b->node1 = fits && !b->persistent ? lbm::node_height(tiles8, 1, b->cus) : 0;
-    b->nodek = fits && b->kstep == 2 ? lbm::node_height(tiles8_k, 2, b->cus) : 0;
-    b->node1_tiles = b->nodek_tiles = 0;
+    const int rows = b->tile_auto ? 0 : b->tile_rows;
+    b->node1 = !b->persistent && lbm::node_fits(b->storage, nodes, 1, rows) ? lbm::node_height(tiles8, 1, b->cus) : 0;
+    b->nodek = b->kstep == 2 && lbm::node_fits(b->storage, nodes, 2, rows) ? lbm::node_height(tiles8_k, 2, b->cus) : 0;
+    b->node1_tiles = b->nodek_tiles = b->node1_wgs = b->nodek_wgs = 0;
     // a channel's chunks; its tiles, or for rectangles the channel, go to the list
-    auto list = [&](int i, int cols, int node, int &node_tiles, int32_t &chunks, std::vector<uint32_t> &out) {
+    auto list = [&](int i, int cols, int node, int &node_tiles, int &node_wgs, int32_t &chunks,
+                    std::vector<uint32_t> &out) {
         const int strips = (b->g[i].nx + cols - 1) / cols;
         chunks = node ? (b->g[i].ny + node - 1) / node : chunks_for(b->g[i].ny, b->tile_rows);
         if (node) {
             node_tiles = std::max(node_tiles, (strips * chunks + 7) / 8 * 8);
+            node_wgs += strips * chunks;
             out.push_back((uint32_t)i);
             return;
         }
@@ -245,10 +248,11 @@ lbm_status upload_tiles(lbm_batch *b) {
     };
     const int kcols = b->kbx - 2 * (2 * std::max(b->kstep, 2) - 1);   // output columns of a multi-step strip
     for (int i : order) {
-        list(i, b->node1 ? lbm::node_columns(1) : b->block_x, b->node1, b->node1_tiles, b->desc[i].chunks, b->host_tiles);
+        list(i, b->node1 ? lbm::node_columns(1) : b->block_x, b->node1, b->node1_tiles, b->node1_wgs,
+             b->desc[i].chunks, b->host_tiles);
         if (b->kstep > 1)
-            list(i, b->nodek ? lbm::node_columns(2) : kcols, b->nodek, b->nodek_tiles, b->desc[i].chunks_k,
-                 b->host_tiles_k);
+            list(i, b->nodek ? lbm::node_columns(2) : kcols, b->nodek, b->nodek_tiles, b->nodek_wgs,
+                 b->desc[i].chunks_k, b->host_tiles_k);
     }
     if (b->host_tiles.size() > b->max_tiles || b->host_tiles_k.size() > b->max_tiles)
         return bfail(b, LBM_EINVAL, "tile list overflow");
@@ -289,6 +293,8 @@ hipError_t enqueue_step(lbm_batch *b, hipStream_t s, int slot, int parity, int g
     a.rows = b->tile_rows;
     a.node = b->node1;
     a.node_tiles = b->node1_tiles;
+    a.node_wgs = b->node1_wgs;
+    a.cus = b->cus;
     a.rng = b->d_rng;
     return lbm::launch_batch_step(b->storage, a, b->block_x, grid, s);
 }
@@ -307,6 +313,8 @@ hipError_t enqueue_stepk(lbm_batch *b, hipStream_t s, int parity) {
     a.rows = b->tile_rows;
     a.node = b->nodek;
     a.node_tiles = b->nodek_tiles;
+    a.node_wgs = b->nodek_wgs;
+    a.cus = b->cus;
     a.rng = b->d_rng;
     return lbm::launch_batch_stepk(b->storage, a, b->kbx, b->kstep, s);
 }

@@ -60,6 +60,7 @@ struct StepArgs {
     // to (gx, gy); NULL for none (fused kernel, BGK, nearest rounding only).
     const float *acc;
     int32_t node;              // rows per workgroup of a rectangle launch (chunks of them; 0: a march)
+    int32_t cus;               // compute units of the device
 };
 
 // One channel of a batch: its lattice, model and device arrays.
@@ -89,6 +90,8 @@ struct BatchStepArgs {
     int32_t node;              // rows per workgroup of a rectangle launch (0: a march); tiles then
                                // holds the ntiles active channels
     int32_t node_tiles;        // workgroups per channel, a multiple of 8
+    int32_t node_wgs;          // workgroups with a tile, in all channels
+    int32_t cus;               // compute units of the device
     uint32_t *rng;             // two-slot step counter of stochastic rounding (slot parity is read)
 };
 
@@ -100,10 +103,10 @@ int step_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
 hipError_t launch_step8(int storage, const StepArgs &a, int block_x, hipStream_t s);
 int step8_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
 // Rectangle launches (k_node, k_batch_node) of k = 1 or 2 steps: whether lattices
-// whose population buffers hold `bytes` run them when chunks of `rows` rows (0:
-// automatic) are asked for; the columns that a workgroup stores; and the rows,
-// from the number of tiles of the lowest height.
-bool node_fits(int64_t bytes, int rows);
+// of `nodes` nodes in all run them when chunks of `rows` rows (0: automatic) are
+// asked for; the columns that a workgroup stores; and the rows, from the number
+// of tiles of the lowest height.
+bool node_fits(int storage, int64_t nodes, int k, int rows);
 int node_columns(int k);
 int64_t node_tiles8(int nx, int ny, int k);
 int node_height(int64_t tiles8, int k, int cus);

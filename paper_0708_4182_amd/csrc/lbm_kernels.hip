@@ -724,17 +724,21 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8, 8))
 // latency on small lattices (128 x 64, FP32: 3.4 us a launch at K = 1 and 4.3
 // at K = 2) and by vector-ALU issue and the halo (1.8 times the stored nodes
 // are pulled at K = 2, R = 2) on large ones.  us per step against the best march
-// of the same K: FP32 128 x 64 K = 2 2.1 (4.5), 1024 x 128 3.3 (6.5), 2048 x 768
-// 13.9 (16.5), TRT 3001 x 517 16.6 (18.9); BF16 2048 x 500 K = 1 11.5 (16.1).
+// of the same K: FP32 128 x 64 K = 2 2.1 (4.5), 1024 x 128 3.4 (6.5), 2048 x 768
+// 12.6 (16.5), TRT 3001 x 517 15.0 (18.9); BF16 2048 x 500 K = 1 11.5 (16.1).
+// (The last three 13.9, 16.6 and 11.5 while the rest population and padding went
+// through LDS too and three workgroups, not four, fitted a compute unit.)
 // R = 4 gained 7% in 16-bit storage at 2M nodes and lost 50% in FP32; K = 3 was
 // no faster anywhere.
 constexpr int NODE_BX = 512;
 template <int S, int K, int R> struct Node {
     static constexpr int H = 2 * K - 1;
     static constexpr int NR = R * NODE_BX / 64;
-    static constexpr int PAD = 64;                                 // floats in front of and behind phi and each F plane
-    static constexpr int PLANE = NR * 64 + 2 * PAD;
-    static constexpr size_t lds = PLANE * sizeof(float) + (K > 1 ? 9 * PLANE * sizeof(typename Codec<S>::T) : 0);
+    static constexpr int PLANE = NR * 64;
+    static constexpr int PAD = 65;       // values read past either end (by threads whose results are unused)
+    // phi, then below the last level the planes of directions 1 .. 8
+    static constexpr size_t lds = PLANE * sizeof(float) + 2 * PAD * sizeof(float) +
+                                  (K > 1 ? 8 * PLANE * sizeof(typename Codec<S>::T) : 0);
 };
 
 template <int S, bool TRT, bool SR, bool EXT, int K, int R>
@@ -760,7 +764,7 @@ __device__ __forceinline__ void node_tile(const StepArgs &a, int x0, int y0, int
     const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == (uint32_t)nx - 1 ? 0 : x + 1;
     const uint32_t v0 = x * E, vm = xm * E, vp = xp * E;
     float *phi = reinterpret_cast<float *>(lds) + N::PAD;
-    T *F = reinterpret_cast<T *>(lds + PLANE * sizeof(float)) + N::PAD;
+    T *F = reinterpret_cast<T *>(phi + PLANE) - PLANE;      // direction q at q PLANE; the rest population stays in its thread
 
     // rows of the tile that exist (the chunk and its halo); rows below them are not computed
     const int rows = y1 - y0 + 2 * H;
@@ -818,7 +822,7 @@ __device__ __forceinline__ void node_tile(const StepArgs &a, int x0, int y0, int
         }
     }
 
-    float d[R][9], s[R], jx[R], jy[R];
+    float d[R][9], s[R], jx[R], jy[R], rest[R];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         // level k: populations and phi of the rows [2k, rows - 2k)
@@ -831,8 +835,8 @@ __device__ __forceinline__ void node_tile(const StepArgs &a, int x0, int y0, int
                 for (int q = 0; q < 9; ++q) d[j][q] = C::dec(raw[j][q]);
             } else {
                 const T *f = F + r * 64 + lane;
+                d[j][0] = rest[j];
                 if (__builtin_amdgcn_ballot_w64((fl[j] & 0xFFu) != 0u) == 0) {
-                    d[j][0] = C::dec(f[0]);
                     d[j][1] = C::dec(f[1 * PLANE - 1]);
                     d[j][2] = C::dec(f[2 * PLANE - 64]);
                     d[j][3] = C::dec(f[3 * PLANE + 1]);
@@ -845,7 +849,6 @@ __device__ __forceinline__ void node_tile(const StepArgs &a, int x0, int y0, int
                     auto from = [&](int q, int o, uint32_t bit, int off) {
                         d[j][q] = C::dec(f[(fl[j] & bit) ? o * PLANE : q * PLANE + off]);
                     };
-                    d[j][0] = C::dec(f[0]);
                     from(1, 3, 0x04u, -1);
                     from(2, 4, 0x08u, -64);
                     from(3, 1, 0x01u, 1);
@@ -888,7 +891,8 @@ __device__ __forceinline__ void node_tile(const StepArgs &a, int x0, int y0, int
             }
             if (k < K - 1) {
 #pragma unroll
-                for (int q = 0; q < 9; ++q) F[q * PLANE + r * 64 + lane] = e[q];
+                for (int q = 1; q < 9; ++q) F[q * PLANE + r * 64 + lane] = e[q];
+                rest[j] = C::dec(e[0]);
             } else if (out_col && !(fl[j] & FL_SOLID)) {
 #pragma unroll
                 for (int q = 0; q < 9; ++q) bstore<0>(rd, v0, ((uint32_t)q * plane + (uint32_t)yr[j] * pitch) * E, e[q]);
@@ -2410,11 +2414,14 @@ StepKernel step_kernel(int storage, bool trt, bool sr) {
     }
 }
 
-// Rectangles instead of a march where both population buffers fit the 256 MB
-// of Infinity Cache, which then serves the halo, and no tall chunk is asked
-// for.  us per step, rectangles against the best march: FP32 3072 x 1152 (255
-// MB) K = 1 41.3 / 57.3 and K = 2 25.8 / 26.7, FP16 3072 x 2304 (255 MB) 60.1 / 63.1
-// and 46 / 43; above, FP32 4096 x 1024 66.4 / 63.8 and 42.3 / 39.4.
+// Rectangles instead of a march where no tall chunk is asked for and the
+// lattice is small: K = 1, bound by memory, while both population buffers fit
+// the 256 MB of Infinity Cache, which then serves the halo; K = 2, bound by the
+// recomputed halo, while buffers of FP32 would.  us per step, rectangles / best
+// march: K = 1 FP32 3072 x 1152 (255 MB) 41.6 / 59, 4096 x 1152 (340 MB) 80 / 73,
+// FP16 3072 x 2304 (255 MB) 60 / 63, 4096 x 2048 (302 MB) 77 / 72; K = 2 FP32 3072
+// x 1152 25.7 / 26.7, 4096 x 1024 38.1 / 37.9, FP16 2048 x 1536 22.7 / 24.1, 3072 x
+// 2304 46.7 / 42.9.
 // The tile is 8 rows high while that leaves at most 3 (K = 1) or 2 workgroups per
 // compute unit, 16 above: us per step at 8 and 16 rows, K = 1: 1024 x 128 4.9 / 5.2,
 // 1024 x 256 6.4 / 6.9, FP16 1024 x 512 9.1 / 8.2; K = 2: 128 x 64 2.1 / 2.9, 512 x 96
@@ -2422,7 +2429,9 @@ StepKernel step_kernel(int storage, bool trt, bool sr) {
 constexpr int64_t NODE_BYTES = 256000000;
 constexpr int NODE_ROWS = 16;
 int node_columns(int k) { return 64 - 2 * (2 * k - 1); }
-bool node_fits(int64_t bytes, int rows) { return bytes <= NODE_BYTES && rows <= NODE_ROWS; }
+bool node_fits(int storage, int64_t nodes, int k, int rows) {
+    return rows <= NODE_ROWS && nodes * 18 * (k == 2 || storage == ST_F32 ? 4 : 2) <= NODE_BYTES;
+}
 int64_t node_tiles8(int nx, int ny, int k) {
     const int rows = 8 - 2 * (2 * k - 1);
     return (int64_t)((nx + node_columns(k) - 1) / node_columns(k)) * ((ny + rows - 1) / rows);
@@ -2431,10 +2440,19 @@ int node_height(int64_t tiles8, int k, int cus) {
     return (tiles8 <= (int64_t)(k == 1 ? 3 : 2) * cus ? 8 : 16) - 2 * (2 * k - 1);
 }
 
+// LDS asked for by a rectangle launch of wgs workgroups: what it needs, or, if
+// they all fit the chip at once, so much that no more than the average share a
+// compute unit.  Left alone they pack unevenly: 12 channels of 256 x 80 and 256 x
+// 160, 720 workgroups, 4 resident at most: 6.3 us per step, at most 3: 5.6.
+size_t spread_lds(size_t need, int64_t wgs, int cus) {
+    const int64_t per = (wgs + cus - 1) / std::max(cus, 1);
+    return per <= 3 ? std::max(need, (size_t)(160 * 1024 / (per + 1) + 1280)) : need;
+}
+
 // A rectangle launch: the lowest tile that holds the chunks and their halo.
 template <int S, bool TRT, bool SR, bool EXT, int K, int R>
 hipError_t launch_node_r(const StepArgs &a, hipStream_t s) {
-    k_node<S, TRT, SR, EXT, K, R><<<8u * (unsigned)a.tiles_per_xcd, NODE_BX, Node<S, K, R>::lds, s>>>(a);
+    k_node<S, TRT, SR, EXT, K, R><<<8u * (unsigned)a.tiles_per_xcd, NODE_BX, spread_lds(Node<S, K, R>::lds, a.ntiles, a.cus), s>>>(a);
     return hipGetLastError();
 }
 template <int S, bool TRT, bool SR, bool EXT, int K>
@@ -2799,9 +2817,11 @@ template <int S, bool TRT, bool SR, int K>
 hipError_t launch_batch_node_k(const BatchStepArgs &a, hipStream_t s) {
     const dim3 grid(a.node_tiles, a.ntiles);
     if (a.node + 2 * Node<S, K, 1>::H <= Node<S, K, 1>::NR)
-        k_batch_node<S, TRT, SR, K, 1><<<grid, NODE_BX, Node<S, K, 1>::lds, s>>>(a.descs, a.tiles, a.parity, a.rng);
+        k_batch_node<S, TRT, SR, K, 1><<<grid, NODE_BX, spread_lds(Node<S, K, 1>::lds, a.node_wgs, a.cus), s>>>(
+            a.descs, a.tiles, a.parity, a.rng);
     else if (a.node + 2 * Node<S, K, 2>::H <= Node<S, K, 2>::NR)
-        k_batch_node<S, TRT, SR, K, 2><<<grid, NODE_BX, Node<S, K, 2>::lds, s>>>(a.descs, a.tiles, a.parity, a.rng);
+        k_batch_node<S, TRT, SR, K, 2><<<grid, NODE_BX, spread_lds(Node<S, K, 2>::lds, a.node_wgs, a.cus), s>>>(
+            a.descs, a.tiles, a.parity, a.rng);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
