@@ -44,10 +44,14 @@ struct BatchLayout {
     size_t max_tiles;
 };
 
-// Largest possible tile count: strips of 64 columns, chunks of at least 8 rows.
+// Largest possible tile count of a march: strips of 64 columns, chunks of at least 8 rows.
 size_t tile_bound(const lbm_params &p) {
     return (size_t)((p.nx + 63) / 64) * (size_t)(p.ny / 8 + 1);
 }
+
+// Largest possible length of a tile list: rectangles of two steps, at their
+// lowest (never fewer than tile_bound).
+size_t list_bound(const lbm_params &p) { return (size_t)lbm::node_tiles8(p.nx, p.ny, 2); }
 
 bool make_batch_layout(int n, const lbm_params *p, BatchLayout &L, std::string &why) {
     if (n <= 0 || n > 65535) {
@@ -98,7 +102,7 @@ bool make_batch_layout(int n, const lbm_params *p, BatchLayout &L, std::string &
         off += align_up(plane * 2, kAlign);
         L.rowplain.push_back(off);
         off += align_up(4 * (size_t)((g.ny + 31) / 32), kAlign);
-        L.max_tiles += tile_bound(p[i]);
+        L.max_tiles += list_bound(p[i]);
         L.buf_bytes_max = std::max(L.buf_bytes_max, align_up(bytes, kAlign));
     }
     L.descs = off;
@@ -151,8 +155,6 @@ struct lbm_batch {
     int tile_rows = 32;
     bool tile_auto = true;             // no tile was asked for
     int node1 = 0, nodek = 0;          // rows per workgroup of rectangle launches of one and of kstep steps (0: march)
-    int node1_tiles = 0, nodek_tiles = 0;   // their workgroups per channel
-    int node1_wgs = 0, nodek_wgs = 0;       // ... and those with a tile, in all
     int ntiles = 0;
     int kstep = 1;                     // time steps per launch: 1, or 2 / 3 (k_batch_tilesk)
     int kbx = 256;                     // block_x of the multi-step kernel (256 or 512)
@@ -232,27 +234,19 @@ lbm_status upload_tiles(lbm_batch *b) {
     const int rows = b->tile_auto ? 0 : b->tile_rows;
     b->node1 = !b->persistent && lbm::node_fits(b->storage, nodes, 1, rows) ? lbm::node_height(tiles8, 1, b->cus) : 0;
     b->nodek = b->kstep == 2 && lbm::node_fits(b->storage, nodes, 2, rows) ? lbm::node_height(tiles8_k, 2, b->cus) : 0;
-    b->node1_tiles = b->nodek_tiles = b->node1_wgs = b->nodek_wgs = 0;
-    // a channel's chunks; its tiles, or for rectangles the channel, go to the list
-    auto list = [&](int i, int cols, int node, int &node_tiles, int &node_wgs, int32_t &chunks,
-                    std::vector<uint32_t> &out) {
+    // A channel's chunks; its tiles go to the list.  16 bits hold a tile's index:
+    // make_batch_layout bounds those of a march, and a channel that node_fits and
+    // is not too large for it has at most 52,429 rectangles (3 x 524,280 nodes).
+    auto list = [&](int i, int cols, int node, int32_t &chunks, std::vector<uint32_t> &out) {
         const int strips = (b->g[i].nx + cols - 1) / cols;
         chunks = node ? (b->g[i].ny + node - 1) / node : chunks_for(b->g[i].ny, b->tile_rows);
-        if (node) {
-            node_tiles = std::max(node_tiles, (strips * chunks + 7) / 8 * 8);
-            node_wgs += strips * chunks;
-            out.push_back((uint32_t)i);
-            return;
-        }
         for (int t = 0; t < strips * chunks; ++t) out.push_back(((uint32_t)i << 16) | (uint32_t)t);
     };
     const int kcols = b->kbx - 2 * (2 * std::max(b->kstep, 2) - 1);   // output columns of a multi-step strip
     for (int i : order) {
-        list(i, b->node1 ? lbm::node_columns(1) : b->block_x, b->node1, b->node1_tiles, b->node1_wgs,
-             b->desc[i].chunks, b->host_tiles);
+        list(i, b->node1 ? lbm::node_columns(1) : b->block_x, b->node1, b->desc[i].chunks, b->host_tiles);
         if (b->kstep > 1)
-            list(i, b->nodek ? lbm::node_columns(2) : kcols, b->nodek, b->nodek_tiles, b->nodek_wgs,
-                 b->desc[i].chunks_k, b->host_tiles_k);
+            list(i, b->nodek ? lbm::node_columns(2) : kcols, b->nodek, b->desc[i].chunks_k, b->host_tiles_k);
     }
     if (b->host_tiles.size() > b->max_tiles || b->host_tiles_k.size() > b->max_tiles)
         return bfail(b, LBM_EINVAL, "tile list overflow");
@@ -292,8 +286,6 @@ hipError_t enqueue_step(lbm_batch *b, hipStream_t s, int slot, int parity, int g
     a.sround = b->sround ? 1 : 0;
     a.rows = b->tile_rows;
     a.node = b->node1;
-    a.node_tiles = b->node1_tiles;
-    a.node_wgs = b->node1_wgs;
     a.cus = b->cus;
     a.rng = b->d_rng;
     return lbm::launch_batch_step(b->storage, a, b->block_x, grid, s);
@@ -312,8 +304,6 @@ hipError_t enqueue_stepk(lbm_batch *b, hipStream_t s, int parity) {
     a.sround = b->sround ? 1 : 0;
     a.rows = b->tile_rows;
     a.node = b->nodek;
-    a.node_tiles = b->nodek_tiles;
-    a.node_wgs = b->nodek_wgs;
     a.cus = b->cus;
     a.rng = b->d_rng;
     return lbm::launch_batch_stepk(b->storage, a, b->kbx, b->kstep, s);

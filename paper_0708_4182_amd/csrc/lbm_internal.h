@@ -87,10 +87,7 @@ struct BatchStepArgs {
     int32_t trt;               // collision operator of every channel (Model::trt)
     int32_t sround;            // rounding of every channel (Model::sround)
     int32_t rows;              // rows per tile asked for (multi-step kernel: selects its form)
-    int32_t node;              // rows per workgroup of a rectangle launch (0: a march); tiles then
-                               // holds the ntiles active channels
-    int32_t node_tiles;        // workgroups per channel, a multiple of 8
-    int32_t node_wgs;          // workgroups with a tile, in all channels
+    int32_t node;              // rows per workgroup of a rectangle launch (0: a march)
     int32_t cus;               // compute units of the device
     uint32_t *rng;             // two-slot step counter of stochastic rounding (slot parity is read)
 };

@@ -2321,30 +2321,35 @@ __global__ void __launch_bounds__(BX) __attribute__((amdgpu_waves_per_eu(stepk_w
     else stepk_tile<S, TRT, SR, BX, K>(a, x0, y0, y1, (chunk & 1) == 0, ldsk, mix);
 }
 
-// The batched step of 1 or 2 time steps by rectangles of nodes (node_tile):
-// channel ids[blockIdx.y], its tiles mapped to XCDs in contiguous ranges;
-// workgroups past a channel's tiles end at once.  Chosen as for a single
+// The batched step of 1 or 2 time steps by rectangles of nodes (node_tile), one
+// workgroup per tile of the list, a tile is (channel << 16) | (chunk * strips +
+// strip), tiles mapped to XCDs in contiguous ranges.  Chosen as for a single
 // lattice, on the buffers of all active channels.  12 channels of the flux study
-// (FP32, 200 steps): 18 us per step by the best march, 6.3 so.
+// (FP32, 60-step graphs): 18 us per step by the best march, 5.8 so.  One channel of
+// 4096 x 256 beside 200 of 64 x 32, one step per launch: 73 us by the march, 23 so;
+// 157 with a grid of the largest channel's tiles x channels, whose 257,000
+// workgroups were nearly all empty.
 template <int S, bool TRT, bool SR, int K, int R>
 __global__ void __launch_bounds__(NODE_BX) k_batch_node(const ChannelDesc *__restrict__ descs,
-                                                        const uint32_t *__restrict__ ids, int parity, uint32_t *rng) {
+                                                        const uint32_t *__restrict__ tiles, int ntiles,
+                                                        int tiles_per_xcd, int parity, uint32_t *rng) {
     extern __shared__ char ldsk[];
     uint32_t mix[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) mix[k] = 0u;
     if constexpr (SR) {
         const uint32_t count = rng[parity];
-        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) rng[parity ^ 1] = count + (uint32_t)K;
+        if (blockIdx.x == 0 && threadIdx.x == 0) rng[parity ^ 1] = count + (uint32_t)K;
 #pragma unroll
         for (int k = 0; k < K; ++k) mix[k] = lowbias32(count + (uint32_t)k + 0x9e3779b9u);
     }
-    const ChannelDesc *d = descs + ids[blockIdx.y];
+    const int at = (int)(blockIdx.x & 7u) * tiles_per_xcd + (int)(blockIdx.x >> 3);
+    if (at >= ntiles) return;       // uniform, before any barrier
+    const uint32_t packed = __builtin_amdgcn_readfirstlane(tiles[at]);
+    const ChannelDesc *d = descs + (packed >> 16);
     constexpr int COLS = 64 - 2 * Node<S, K, R>::H;
     const int chunks = K == 1 ? d->chunks : d->chunks_k, strips = (d->g.nx + COLS - 1) / COLS;
-    const int ntiles = strips * chunks, per = (ntiles + 7) / 8;
-    const int tile = (int)(blockIdx.x & 7u) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || tile >= ntiles) return;    // uniform, before any barrier
+    const int tile = (int)(packed & 0xFFFFu);
     StepArgs a;
     a.src = parity ? d->buf[1] : d->buf[0];
     a.dst = const_cast<void *>(parity ? d->buf[0] : d->buf[1]);
@@ -2815,13 +2820,13 @@ auto batch_kernel(int storage, bool trt, bool sr) -> decltype(batch_k<QUEUE, ST_
 
 template <int S, bool TRT, bool SR, int K>
 hipError_t launch_batch_node_k(const BatchStepArgs &a, hipStream_t s) {
-    const dim3 grid(a.node_tiles, a.ntiles);
+    const int per = (a.ntiles + 7) / 8;
     if (a.node + 2 * Node<S, K, 1>::H <= Node<S, K, 1>::NR)
-        k_batch_node<S, TRT, SR, K, 1><<<grid, NODE_BX, spread_lds(Node<S, K, 1>::lds, a.node_wgs, a.cus), s>>>(
-            a.descs, a.tiles, a.parity, a.rng);
+        k_batch_node<S, TRT, SR, K, 1><<<8 * per, NODE_BX, spread_lds(Node<S, K, 1>::lds, a.ntiles, a.cus), s>>>(
+            a.descs, a.tiles, a.ntiles, per, a.parity, a.rng);
     else if (a.node + 2 * Node<S, K, 2>::H <= Node<S, K, 2>::NR)
-        k_batch_node<S, TRT, SR, K, 2><<<grid, NODE_BX, spread_lds(Node<S, K, 2>::lds, a.node_wgs, a.cus), s>>>(
-            a.descs, a.tiles, a.parity, a.rng);
+        k_batch_node<S, TRT, SR, K, 2><<<8 * per, NODE_BX, spread_lds(Node<S, K, 2>::lds, a.ntiles, a.cus), s>>>(
+            a.descs, a.tiles, a.ntiles, per, a.parity, a.rng);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -242,6 +242,42 @@ def test_batch_rectangles_bitwise(lbm, kernel, storage, rounding, collision, tal
         np.testing.assert_array_equal(x, y)
 
 
+@pytest.mark.parametrize("kernel", ["fused", "two"])
+@pytest.mark.parametrize("storage,rounding", [(0, 0), (1, 1)])
+def test_uneven_batch_untuned(lbm, storage, rounding, kernel):
+    """One long channel beside 200 small ones, untuned: the rectangles that such a
+    batch runs give the march's bits and are no slower than the march (best of
+    alternating runs, a quarter of the march's time allowed for noise)."""
+    import torch
+    cases = []
+    for k, (nx, ny) in enumerate([(4096, 256)] + [(64, 32)] * 200):
+        c = I.random_channel_case(nx=nx, ny=ny, seed=1 + k % 7)
+        c.params = c.params.replace(storage=storage, rounding=rounding)
+        cases.append(c)
+    rect, march = lbm.Batch(cases), lbm.Batch(cases)
+    march.set_tile(256, 33)
+    best = {}
+    for b in (rect, march):
+        b.set_kernel(kernel)
+        b.step(3)
+    for i in (0, 1, 200):
+        for x, y in zip(rect.moments(i), march.moments(i)):
+            np.testing.assert_array_equal(x, y, err_msg=f"channel {i}")
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for b in (rect, march):
+        b.set_graph(20)
+        b.step(20)
+    for _ in range(5):
+        for b in (rect, march):
+            e0.record(b.stream)
+            b.step(40)
+            e1.record(b.stream)
+            torch.cuda.synchronize()
+            best[b] = min(best.get(b, np.inf), e0.elapsed_time(e1) / 40)
+    print(f"{kernel} storage {storage}: rectangles {1e3 * best[rect]:.1f} us per step, march {1e3 * best[march]:.1f}")
+    assert best[rect] <= 1.25 * best[march]
+
+
 @pytest.mark.parametrize("kernel,graph_steps", [("two", 2), ("two", 10), ("three", 4), ("three", 10)])
 def test_multi_step_graph_equals_eager(lbm, kernel, graph_steps):
     """Replays of graphs of k-step launches plus single-step remainders (two
