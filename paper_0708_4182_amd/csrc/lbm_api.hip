@@ -530,7 +530,6 @@ lbm::StepArgs step_args_for(lbm_sim *s, int kernel, int &cache) {
     a.par = s->cur;
     a.acc = s->acc;
     a.node = node;
-    a.cus = s->cus;
     return a;
 }
 

@@ -286,7 +286,6 @@ hipError_t enqueue_step(lbm_batch *b, hipStream_t s, int slot, int parity, int g
     a.sround = b->sround ? 1 : 0;
     a.rows = b->tile_rows;
     a.node = b->node1;
-    a.cus = b->cus;
     a.rng = b->d_rng;
     return lbm::launch_batch_step(b->storage, a, b->block_x, grid, s);
 }
@@ -304,7 +303,6 @@ hipError_t enqueue_stepk(lbm_batch *b, hipStream_t s, int parity) {
     a.sround = b->sround ? 1 : 0;
     a.rows = b->tile_rows;
     a.node = b->nodek;
-    a.cus = b->cus;
     a.rng = b->d_rng;
     return lbm::launch_batch_stepk(b->storage, a, b->kbx, b->kstep, s);
 }

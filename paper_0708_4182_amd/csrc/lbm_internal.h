@@ -60,7 +60,6 @@ struct StepArgs {
     // to (gx, gy); NULL for none (fused kernel, BGK, nearest rounding only).
     const float *acc;
     int32_t node;              // rows per workgroup of a rectangle launch (chunks of them; 0: a march)
-    int32_t cus;               // compute units of the device
 };
 
 // One channel of a batch: its lattice, model and device arrays.
@@ -88,7 +87,6 @@ struct BatchStepArgs {
     int32_t sround;            // rounding of every channel (Model::sround)
     int32_t rows;              // rows per tile asked for (multi-step kernel: selects its form)
     int32_t node;              // rows per workgroup of a rectangle launch (0: a march)
-    int32_t cus;               // compute units of the device
     uint32_t *rng;             // two-slot step counter of stochastic rounding (slot parity is read)
 };
 

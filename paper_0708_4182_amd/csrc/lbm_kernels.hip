@@ -2445,19 +2445,10 @@ int node_height(int64_t tiles8, int k, int cus) {
     return (tiles8 <= (int64_t)(k == 1 ? 3 : 2) * cus ? 8 : 16) - 2 * (2 * k - 1);
 }
 
-// LDS asked for by a rectangle launch of wgs workgroups: what it needs, or, if
-// they all fit the chip at once, so much that no more than the average share a
-// compute unit.  Left alone they pack unevenly: 12 channels of 256 x 80 and 256 x
-// 160, 720 workgroups, 4 resident at most: 6.3 us per step, at most 3: 5.6.
-size_t spread_lds(size_t need, int64_t wgs, int cus) {
-    const int64_t per = (wgs + cus - 1) / std::max(cus, 1);
-    return per <= 3 ? std::max(need, (size_t)(160 * 1024 / (per + 1) + 1280)) : need;
-}
-
 // A rectangle launch: the lowest tile that holds the chunks and their halo.
 template <int S, bool TRT, bool SR, bool EXT, int K, int R>
 hipError_t launch_node_r(const StepArgs &a, hipStream_t s) {
-    k_node<S, TRT, SR, EXT, K, R><<<8u * (unsigned)a.tiles_per_xcd, NODE_BX, spread_lds(Node<S, K, R>::lds, a.ntiles, a.cus), s>>>(a);
+    k_node<S, TRT, SR, EXT, K, R><<<8u * (unsigned)a.tiles_per_xcd, NODE_BX, Node<S, K, R>::lds, s>>>(a);
     return hipGetLastError();
 }
 template <int S, bool TRT, bool SR, bool EXT, int K>
@@ -2822,10 +2813,10 @@ template <int S, bool TRT, bool SR, int K>
 hipError_t launch_batch_node_k(const BatchStepArgs &a, hipStream_t s) {
     const int per = (a.ntiles + 7) / 8;
     if (a.node + 2 * Node<S, K, 1>::H <= Node<S, K, 1>::NR)
-        k_batch_node<S, TRT, SR, K, 1><<<8 * per, NODE_BX, spread_lds(Node<S, K, 1>::lds, a.ntiles, a.cus), s>>>(
+        k_batch_node<S, TRT, SR, K, 1><<<8 * per, NODE_BX, Node<S, K, 1>::lds, s>>>(
             a.descs, a.tiles, a.ntiles, per, a.parity, a.rng);
     else if (a.node + 2 * Node<S, K, 2>::H <= Node<S, K, 2>::NR)
-        k_batch_node<S, TRT, SR, K, 2><<<8 * per, NODE_BX, spread_lds(Node<S, K, 2>::lds, a.ntiles, a.cus), s>>>(
+        k_batch_node<S, TRT, SR, K, 2><<<8 * per, NODE_BX, Node<S, K, 2>::lds, s>>>(
             a.descs, a.tiles, a.ntiles, per, a.parity, a.rng);
     else return hipErrorInvalidValue;
     return hipGetLastError();
