@@ -245,8 +245,13 @@ lbm_status lbm_set_accel_field(lbm_sim *sim, const float *acc);
  * for the split kernel) and about
  * rows_per_block rows marched by one workgroup; 0 picks as many row chunks as
  * fill one wave of resident workgroups (chunks of at least 8 rows).  Results
- * do not depend on the tile (bitwise).  Default 256 x 0.  Takes effect at the
- * next lbm_step. */
+ * do not depend on the tile (bitwise).  Default 256 x 0, which leaves the form
+ * to the library: LBM_KERNEL_FUSED and LBM_KERNEL_TWO then advance a small
+ * lattice by rectangles of at most 62 x 14 nodes, one workgroup each, instead of
+ * marching (LBM_KERNEL_FUSED while the two population buffers take at most
+ * 256 MB, LBM_KERNEL_TWO up to 3.5 million nodes), and so do the single steps
+ * that a multi-step kernel leaves, at any tile.  Any other tile is marched as
+ * asked.  Takes effect at the next lbm_step. */
 lbm_status lbm_set_tile(lbm_sim *sim, int32_t block_x, int32_t rows_per_block);
 
 /* Step kernel.  LBM_KERNEL_FUSED: every thread loads, computes and stores its
@@ -297,7 +302,8 @@ lbm_status lbm_get_tile(const lbm_sim *sim, int32_t *kernel, int32_t *block_x, i
 /* Autotuner: times each candidate (fused kernels: block_x in 64..512 (6 waves)
  * or 128..512 (8 waves); wide
  * kernels: block_x 64..256; split kernel: block_x 128 or 256; rows_per_block
- * in {0, 4, 8, 16, 32, 64, 128}) for `reps`
+ * in {0, 4, 8, 16, 32, 64, 128}; multi-step kernels: block_x 256 or 512, the
+ * same rows and those of whole waves of resident workgroups) for `reps`
  * launches on the current state and keeps the fastest.  The trial launches
  * write only the spare population buffer, so the simulation state and step
  * count are unchanged.  Synchronizes.  The chosen tile and its time per step
@@ -373,7 +379,10 @@ lbm_status lbm_batch_set_forces(lbm_batch *b, int32_t i, double f_elec, double a
 lbm_status lbm_batch_retire(lbm_batch *b, const uint8_t *done);
 
 /* Tile shape: block_x columns (64..512) by about rows_per_tile rows (>= 8).
- * Results do not depend on it (bitwise).  Default 256 x 32. */
+ * Results do not depend on it (bitwise).  Default 256 x 32, which leaves the
+ * form of LBM_KERNEL_FUSED (not persistent) and LBM_KERNEL_TWO to the library as
+ * lbm_set_tile's default does, by the size of all active channels together; any
+ * other tile is marched as asked. */
 lbm_status lbm_batch_set_tile(lbm_batch *b, int32_t block_x, int32_t rows_per_tile);
 
 /* Work distribution of a step launch: persistent != 0 runs a persistent grid
@@ -385,7 +394,8 @@ lbm_status lbm_batch_set_schedule(lbm_batch *b, int32_t persistent);
 /* Steps per launch: LBM_KERNEL_FUSED (one; default), LBM_KERNEL_TWO or
  * LBM_KERNEL_THREE (two or three steps per launch from one workgroup per
  * tile, strips of block_x - 6 or block_x - 10 output columns, block_x 512 if
- * lbm_batch_set_tile chose 512, else 256).  Bitwise the same results as the
+ * lbm_batch_set_tile chose 512, else 256; or rectangles, see
+ * lbm_batch_set_tile).  Bitwise the same results as the
  * one-step kernel, for every storage format, operator and rounding mode.
  * LBM_EINVAL for another value.  Rebuilds the tile list; synchronizes. */
 lbm_status lbm_batch_set_kernel(lbm_batch *b, int32_t kernel);

@@ -22,6 +22,8 @@
 using lbm::Grid;
 using lbm::Model;
 
+constexpr int kBlockX = 256;   // of the default tile (rows 0)
+
 struct lbm_sim {
     lbm_params p{};
     Grid g{};
@@ -41,8 +43,8 @@ struct lbm_sim {
     std::string static_err;             // why static_scratch is NULL, if it is
     int cur = 0;
     int64_t steps = 0;
-    int block_x = 256;
-    int rows = 0;          // rows per chunk; 0 = one wave of resident workgroups
+    int block_x = kBlockX;
+    int rows = 0;          // rows per chunk; 0 = one wave of resident workgroups (see node_rows_for)
     int kernel = LBM_KERNEL_FUSED;
     int cus = 0;           // compute units of the device
     int max_lds = 0;       // LDS bytes one workgroup may use on the device
@@ -473,12 +475,15 @@ int strip_columns(const lbm_sim *s, int kernel) {
     }
 }
 
-// Rows per workgroup of a rectangle launch of the kernel at the handle's tile;
-// 0: its launches march.
+// Rows per workgroup of a rectangle launch of the kernel; 0: its launches march.
+// The default tile leaves the form to the library, any other is marched as
+// asked; it was asked for the handle's kernel, not for the single steps that a
+// multi-step kernel leaves.
 int node_rows_for(const lbm_sim *s, int kernel) {
     const int k = steps_per_launch(kernel);
-    if ((kernel != LBM_KERNEL_FUSED && kernel != LBM_KERNEL_TWO) ||
-        !lbm::node_fits(s->p.storage, (int64_t)s->p.nx * s->p.ny, k, s->rows))
+    const bool asked = kernel == s->kernel && (s->block_x != kBlockX || s->rows != 0);
+    if ((kernel != LBM_KERNEL_FUSED && kernel != LBM_KERNEL_TWO) || asked ||
+        !lbm::node_fits(s->p.storage, (int64_t)s->p.nx * s->p.ny, k))
         return 0;
     return lbm::node_height(lbm::node_tiles8(s->p.nx, s->p.ny, k), k, s->cus);
 }
@@ -886,8 +891,6 @@ lbm_status lbm_autotune(lbm_sim *s, int32_t reps, int32_t *block_x, int32_t *row
             s->rows = r;
             s->chunks = 0;
             s->chunks1 = 0;
-            // rectangle launches are the same at every tile: timed once
-            if (node_rows_for(s, cand.kernel) > 0 && (r > 0 || bx != 256)) continue;
             // trial launches read the current buffer and write the spare one,
             // so the state is left as it was
             lbm::StepArgs a = step_args(s);

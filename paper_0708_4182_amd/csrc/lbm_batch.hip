@@ -32,6 +32,7 @@ void row_plain_mask(int nx, int ny, const std::vector<uint16_t> &fl, std::vector
 namespace {
 constexpr size_t kAlign = 256;
 constexpr int kMaxGraphSteps = 1024;
+constexpr int kBlockX = 256, kTileRows = 32;   // the default tile
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 size_t elem_size(int storage) { return storage == LBM_F32 ? 4 : 2; }
 thread_local std::string g_batch_init_error;
@@ -151,9 +152,8 @@ struct lbm_batch {
     std::vector<int32_t> cur;          // current buffer index per channel
     std::vector<int64_t> steps;
     int parity = 0;                    // current buffer index of the active channels
-    int block_x = 256;
-    int tile_rows = 32;
-    bool tile_auto = true;             // no tile was asked for
+    int block_x = kBlockX;
+    int tile_rows = kTileRows;
     int node1 = 0, nodek = 0;          // rows per workgroup of rectangle launches of one and of kstep steps (0: march)
     int ntiles = 0;
     int kstep = 1;                     // time steps per launch: 1, or 2 / 3 (k_batch_tilesk)
@@ -231,9 +231,13 @@ lbm_status upload_tiles(lbm_batch *b) {
         tiles8 += lbm::node_tiles8(b->g[i].nx, b->g[i].ny, 1);
         tiles8_k += lbm::node_tiles8(b->g[i].nx, b->g[i].ny, 2);
     }
-    const int rows = b->tile_auto ? 0 : b->tile_rows;
-    b->node1 = !b->persistent && lbm::node_fits(b->storage, nodes, 1, rows) ? lbm::node_height(tiles8, 1, b->cus) : 0;
-    b->nodek = b->kstep == 2 && lbm::node_fits(b->storage, nodes, 2, rows) ? lbm::node_height(tiles8_k, 2, b->cus) : 0;
+    // (the default tile leaves the form to the library, any other is marched as
+    // asked; it was asked for the k-step launches, not for the single steps they leave)
+    const bool asked = b->block_x != kBlockX || b->tile_rows != kTileRows;
+    b->node1 = !b->persistent && (!asked || b->kstep > 1) && lbm::node_fits(b->storage, nodes, 1)
+                   ? lbm::node_height(tiles8, 1, b->cus) : 0;
+    b->nodek = b->kstep == 2 && !asked && lbm::node_fits(b->storage, nodes, 2)
+                   ? lbm::node_height(tiles8_k, 2, b->cus) : 0;
     // A channel's chunks; its tiles go to the list.  16 bits hold a tile's index:
     // make_batch_layout bounds those of a march, and a channel that node_fits and
     // is not too large for it has at most 52,429 rectangles (3 x 524,280 nodes).
@@ -644,7 +648,6 @@ lbm_status lbm_batch_set_tile(lbm_batch *b, int32_t block_x, int32_t rows) {
     b->block_x = block_x;
     b->kbx = block_x == 512 ? 512 : 256;
     b->tile_rows = rows;
-    b->tile_auto = false;
     return upload_tiles(b);
 }
 
@@ -722,10 +725,7 @@ lbm_status lbm_batch_autotune(lbm_batch *b, int32_t reps, int32_t *block_x, int3
             b->block_x = c.bx;
             b->kbx = c.bx == 512 ? 512 : 256;
             b->tile_rows = r;
-            b->tile_auto = false;
             if ((st = upload_tiles(b)) != LBM_OK) break;
-            // rectangle launches are the same at every tile: timed once
-            if ((c.kstep > 1 ? b->nodek : b->node1) && (c.bx != 256 || r != kRows[0])) continue;
             if ((c.kstep > 1 ? b->ntiles_k : b->ntiles) == 0) continue;
             const int grid = c.kstep > 1 ? 0 : persistent_grid(b);
             // trial launches read the current buffers and write the spare ones

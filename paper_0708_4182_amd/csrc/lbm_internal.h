@@ -98,10 +98,9 @@ int step_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
 hipError_t launch_step8(int storage, const StepArgs &a, int block_x, hipStream_t s);
 int step8_blocks_per_cu(int storage, int block_x, bool trt, bool sr);
 // Rectangle launches (k_node, k_batch_node) of k = 1 or 2 steps: whether lattices
-// of `nodes` nodes in all run them when chunks of `rows` rows (0: automatic) are
-// asked for; the columns that a workgroup stores; and the rows, from the number
-// of tiles of the lowest height.
-bool node_fits(int storage, int64_t nodes, int k, int rows);
+// of `nodes` nodes in all run them where no tile is asked for; the columns that a
+// workgroup stores; and the rows, from the number of tiles of the lowest height.
+bool node_fits(int storage, int64_t nodes, int k);
 int node_columns(int k);
 int64_t node_tiles8(int nx, int ny, int k);
 int node_height(int64_t tiles8, int k, int cus);

@@ -2419,8 +2419,8 @@ StepKernel step_kernel(int storage, bool trt, bool sr) {
     }
 }
 
-// Rectangles instead of a march where no tall chunk is asked for and the
-// lattice is small: K = 1, bound by memory, while both population buffers fit
+// Rectangles instead of a march where no tile is asked for and the lattice is
+// small: K = 1, bound by memory, while both population buffers fit
 // the 256 MB of Infinity Cache, which then serves the halo; K = 2, bound by the
 // recomputed halo, while buffers of FP32 would.  us per step, rectangles / best
 // march: K = 1 FP32 3072 x 1152 (255 MB) 41.6 / 59, 4096 x 1152 (340 MB) 80 / 73,
@@ -2432,10 +2432,9 @@ StepKernel step_kernel(int storage, bool trt, bool sr) {
 // 1024 x 256 6.4 / 6.9, FP16 1024 x 512 9.1 / 8.2; K = 2: 128 x 64 2.1 / 2.9, 512 x 96
 // 2.9 / 3.3, 1024 x 64 3.5 / 3.5, 1024 x 128 4.6 / 3.5.
 constexpr int64_t NODE_BYTES = 256000000;
-constexpr int NODE_ROWS = 16;
 int node_columns(int k) { return 64 - 2 * (2 * k - 1); }
-bool node_fits(int storage, int64_t nodes, int k, int rows) {
-    return rows <= NODE_ROWS && nodes * 18 * (k == 2 || storage == ST_F32 ? 4 : 2) <= NODE_BYTES;
+bool node_fits(int storage, int64_t nodes, int k) {
+    return nodes * 18 * (k == 2 || storage == ST_F32 ? 4 : 2) <= NODE_BYTES;
 }
 int64_t node_tiles8(int nx, int ny, int k) {
     const int rows = 8 - 2 * (2 * k - 1);

@@ -54,3 +54,54 @@ def test_batch_launches_one_workgroup_per_rectangle(lbm):
         tiles = sum(-(-nx // cols) * -(-ny // rows) for nx, ny in shapes)
         (l,) = launches(lambda: b.step(1 if kernel == "fused" else 2))
         assert l.kernel.startswith("k_batch_node<") and tiles <= l.groups < tiles + 8, (l, tiles)
+
+
+@pytest.mark.parametrize("kernel,tile,form,threads,strips,chunks", [
+    ("fused", (256, 0), "k_node<", 512, 5, 22),       # the default: 62 x 6 rectangles
+    ("fused", (64, 8), "k_step<", 64, 5, 17), ("fused", (512, 16), "k_step<", 512, 1, 9),
+    ("fused", (64, 1), "k_step<", 64, 5, 131), ("fused", (256, 4), "k_step<", 256, 2, 33),
+    ("two", (256, 7), "k_stepk<", 256, 2, 19), ("two", (512, 16), "k_stepk<", 512, 1, 9),
+    ("three", (256, 5), "k_stepk<", 256, 2, 27)])
+def test_tiles_are_marched_as_asked(lbm, kernel, tile, form, threads, strips, chunks):
+    """A tile that was asked for is marched in strips of its columns and chunks of
+    its rows also on a small lattice; only the default tile leaves the form open."""
+    sim = lbm.from_case(case(300, 131))
+    sim.set_kernel(kernel)
+    sim.set_tile(*tile)
+    (l,) = launches(lambda: sim.step({"two": 2, "three": 3}.get(kernel, 1)))
+    assert l.kernel.startswith(form) and l.threads == threads, l
+    assert strips * chunks <= l.groups < strips * chunks + 8, l
+
+
+@pytest.mark.parametrize("kernel,tile", [("two", (256, 8)), ("two", (512, 40)), ("three", (256, 0)), ("three", (512, 16))])
+def test_steps_left_by_a_multi_step_kernel(lbm, kernel, tile):
+    """They take the library's form at any tile."""
+    sim = lbm.from_case(case(300, 131))
+    sim.set_kernel(kernel)
+    sim.set_tile(*tile)
+    k = {"two": 2, "three": 3}[kernel]
+    ls = launches(lambda: sim.step(2 * k - 1))
+    assert [l.kernel.split("<")[0] for l in ls] == ["k_stepk"] + ["k_node"] * (k - 1), ls
+
+
+@pytest.mark.parametrize("tile,form", [((256, 32), "k_batch_node<"), ((256, 16), "march"), ((64, 8), "march"),
+                                       ((128, 32), "march")])
+def test_batch_tiles_are_marched_as_asked(lbm, tile, form):
+    b = lbm.Batch([case(300, 131), case(64, 40)])
+    b.set_tile(*tile)
+    for kernel, march in (("fused", "k_batch_tiles<"), ("two", "k_batch_tilesk<")):
+        b.set_kernel(kernel)
+        (l,) = launches(lambda: b.step(1 if kernel == "fused" else 2))
+        assert l.kernel.startswith(march if form == "march" else form), l
+
+
+def test_autotuners_time_the_march_too(lbm):
+    """On a small lattice and a small batch the tuners try low marches beside the
+    rectangles."""
+    sim = lbm.from_case(case(300, 131))
+    ls = launches(lambda: sim.autotune(reps=1))
+    assert {(l.kernel.split("<")[0], l.threads) for l in ls} >= {("k_node", 512), ("k_step", 64), ("k_step", 256)}
+    assert max(l.groups for l in ls if l.kernel.startswith("k_step<") and l.threads == 64) >= 5 * 33     # 4 rows
+    b = lbm.Batch([case(300, 131), case(64, 40)])
+    ls = launches(lambda: b.autotune(reps=1))
+    assert {l.kernel.split("<")[0] for l in ls} >= {"k_batch_node", "k_batch_tiles", "k_batch_tilesk", "k_batch_step"}
