@@ -502,22 +502,33 @@ lbm::StepArgs step_args_for(lbm_sim *s, int kernel, int &cache) {
             chunks = (s->p.ny + s->rows - 1) / s->rows;
         } else {
             // one wave of resident workgroups, chunks of at least 8 rows
+            auto one_wave = [&](int per_cu) {
+                return std::min(std::max(1, s->cus * per_cu / strips), std::max(1, s->p.ny / 8));
+            };
             int per_cu;
             switch (kernel) {
             case LBM_KERNEL_TWO:
-            case LBM_KERNEL_THREE:
-                per_cu = lbm::stepk_blocks_per_cu(s->p.storage, s->block_x, steps_per_launch(kernel), s->m.trt != 0,
-                                                  s->m.sround != 0);
+            case LBM_KERNEL_THREE: {
+                // of the form that its chunks run: where that of low chunks has more
+                // workgroups resident it wins as long as its own wave stays low (FP32
+                // TRT, two steps, 512 columns, us per step by the waves of the low /
+                // the tall form: 8192 x 500 41 / 48, 8192 x 900 71 / 73, 5000 x 400 23 /
+                // 26, and 8192 x 1000, where both are tall, 84 / 79)
+                auto resident = [&](bool tall) {
+                    return lbm::stepk_blocks_per_cu(s->p.storage, s->block_x, steps_per_launch(kernel), s->m.trt != 0,
+                                                    s->m.sround != 0, tall);
+                };
+                per_cu = resident(false);
+                if (lbm::stepk_tall(s->p.storage, s->p.ny / one_wave(per_cu))) per_cu = resident(true);
                 break;
+            }
             case LBM_KERNEL_SPLIT: per_cu = lbm::split_blocks_per_cu(s->p.storage, s->block_x); break;
             case LBM_KERNEL_WIDE2: per_cu = lbm::wide_blocks_per_cu(s->p.storage, s->block_x, 2); break;
             case LBM_KERNEL_WIDE4: per_cu = lbm::wide_blocks_per_cu(s->p.storage, s->block_x, 4); break;
             case LBM_KERNEL_FUSED8: per_cu = lbm::step8_blocks_per_cu(s->p.storage, s->block_x, s->m.trt != 0, s->m.sround != 0); break;
             default: per_cu = lbm::step_blocks_per_cu(s->p.storage, s->block_x, s->m.trt != 0, s->m.sround != 0); break;
             }
-            const int cap = s->cus * per_cu;
-            chunks = std::max(1, cap / strips);
-            chunks = std::min(chunks, std::max(1, s->p.ny / 8));
+            chunks = one_wave(per_cu);
         }
         cache = std::max(1, std::min(chunks, s->p.ny));
     }
@@ -877,8 +888,10 @@ lbm_status lbm_autotune(lbm_sim *s, int32_t reps, int32_t *block_x, int32_t *row
         if (kst > 1) {
             const int cols = bx - 2 * (2 * kst - 1);
             const int strips = (s->p.nx + cols - 1) / cols;
-            const int per_cu = lbm::stepk_blocks_per_cu(s->p.storage, bx, kst, s->m.trt != 0, s->m.sround != 0);
-            for (int k = 1; k <= per_cu; ++k) {
+            auto resident = [&](bool tall) {
+                return lbm::stepk_blocks_per_cu(s->p.storage, bx, kst, s->m.trt != 0, s->m.sround != 0, tall);
+            };
+            for (int k = 1, most = std::max(resident(false), resident(true)); k <= most; ++k) {
                 const int chunks = std::max(1, (k * s->cus) / strips);
                 const int r = (s->p.ny + chunks - 1) / chunks;
                 if (std::find(rows_list.begin(), rows_list.end(), r) == rows_list.end()) rows_list.push_back(r);

@@ -105,11 +105,13 @@ int node_columns(int k);
 int64_t node_tiles8(int nx, int ny, int k);
 int node_height(int64_t tiles8, int k, int cus);
 // k = 2 or 3 time steps per launch (src -> dst after k steps; strips of
-// block_x - 2 (2k - 1) columns), its LDS per workgroup and its resident
-// workgroups per compute unit.
+// block_x - 2 (2k - 1) columns), its LDS per workgroup, whether chunks of `rows`
+// rows run its form for tall ones, and the resident workgroups of either form per
+// compute unit.
 hipError_t launch_stepk(int storage, const StepArgs &a, int block_x, int k, hipStream_t s);
 size_t stepk_lds_bytes(int storage, int block_x, int k);
-int stepk_blocks_per_cu(int storage, int block_x, int k, bool trt, bool sr);
+bool stepk_tall(int storage, int rows);
+int stepk_blocks_per_cu(int storage, int block_x, int k, bool trt, bool sr, bool tall);
 // The split step (a producer wave streams rows into LDS for block_x compute
 // threads; block_x = 128 or 256) and its resident workgroups per compute unit.
 hipError_t launch_step_split(int storage, const StepArgs &a, int block_x, hipStream_t s);

@@ -2565,8 +2565,8 @@ hipError_t launch_stepk(int storage, const StepArgs &a, int block_x, int k, hipS
     return hipGetLastError();
 }
 
-int stepk_blocks_per_cu(int storage, int block_x, int k, bool trt, bool sr) {
-    const bool tall = storage == ST_F32;
+int stepk_blocks_per_cu(int storage, int block_x, int k, bool trt, bool sr, bool tall) {
+    if (storage != ST_F32) tall = false;
     StepKernel kern = stepk_kernel(storage, block_x, k, trt, sr, tall);
     if (!kern) return 1;
     int n = 0;

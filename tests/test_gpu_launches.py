@@ -105,3 +105,19 @@ def test_autotuners_time_the_march_too(lbm):
     b = lbm.Batch([case(300, 131), case(64, 40)])
     ls = launches(lambda: b.autotune(reps=1))
     assert {l.kernel.split("<")[0] for l in ls} >= {"k_batch_node", "k_batch_tiles", "k_batch_tilesk", "k_batch_step"}
+
+
+@pytest.mark.parametrize("nx,ny,tall,groups", [(4100, 900, "false", 9 * 56), (5000, 900, "false", 10 * 51),
+                                               (4100, 1900, "true", 9 * 28)])
+def test_automatic_rows_fill_the_form_that_runs(lbm, nx, ny, tall, groups):
+    """FP32 TRT, two steps, 512 columns: two workgroups of the form for low chunks
+    are resident per compute unit (256 of them), one of the form for tall chunks;
+    automatic rows give one wave of the form they launch."""
+    import torch
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    sim = lbm.from_case(case(nx, ny, collision=1))
+    sim.set_kernel("two")
+    sim.set_tile(512, 0)
+    (l,) = launches(lambda: sim.step(2))
+    assert l.kernel.startswith("k_stepk<") and l.kernel.endswith(tall + ">"), l
+    assert groups <= l.groups < groups + 8, l
