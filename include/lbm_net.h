@@ -26,8 +26,9 @@
  * the weights W[cout][cin][ky][kx] then the biases b[cout].
  *
  * Conventions are those of lbm.h: lbm_status return codes, no exceptions, the
- * caller owns every array and the 256-byte aligned device workspace, all GPU
- * work runs on the stream given to lbm_net_create.  Tensors x, y and t are
+ * caller owns every array and the 256-byte aligned device workspace, all kernels
+ * run on the stream given to lbm_net_create.  (lbm_net_gradient may copy on a
+ * stream of the handle's own, ordered by events; see there.)  Tensors x, y and t are
  * device FP32 arrays [n][planes][H][W] (x fastest); fluid is a device uint8
  * array [n][H][W], nonzero where the loss counts.  Activations are stored in
  * bf16 (act_bf16 = 1) or FP32 (act_bf16 = 0, the checking build).  With bf16
@@ -87,7 +88,11 @@ lbm_status lbm_net_forward(lbm_net *net, const float *x, float *y, int32_t n);
 /* Loss and gradient with respect to the parameters for n samples; the loss is
  * written to *loss and, if grad_host is not NULL, the gradient to grad_host
  * (param_count floats).  The gradient stays on the device for lbm_net_adam.
- * Synchronous. */
+ * Synchronous.  From 262,144 parameters on, grad_host is filled while the
+ * backward pass runs: the first such call creates a private stream, events and
+ * pinned host memory of the size of the parameters, which the handle keeps until
+ * lbm_net_free.  Where one of them cannot be had, the gradient is copied after
+ * the pass. */
 lbm_status lbm_net_gradient(lbm_net *net, const float *x, const float *t, const uint8_t *fluid, int32_t n,
                             double *loss, float *grad_host);
 
