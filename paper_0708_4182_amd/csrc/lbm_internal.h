@@ -44,7 +44,8 @@ struct StepArgs {
     Model m;
     // Tiling: the lattice is cut into strips of block_x columns, each strip
     // into `chunks` chunks of consecutive rows (sizes differ by at most one);
-    // tile t = strip * chunks + chunk.  Workgroup b runs tile
+    // tile t = strip * chunks + chunk, or chunk * strips + strip in multi-step and
+    // rectangle launches, whose strips share cache lines.  Workgroup b runs tile
     // (b mod 8) * tiles_per_xcd + b / 8, so an XCD gets consecutive tiles.
     int32_t chunks;
     int32_t ntiles;
@@ -73,9 +74,10 @@ struct ChannelDesc {
     const uint32_t *rowplain;  // bit y: every node of row y has the plain flag word (see lbm_kernels.hip)
 };
 
-// Persistent batched step: workgroups take tiles from a queue (one counter
-// per step slot, zeroed before use) until the list is exhausted.  A tile is
-// (channel << 16) | (strip * chunks + chunk).
+// A batched launch: one workgroup per tile, or (one step per launch, persistent)
+// workgroups that take tiles from a queue (one counter per step slot, zeroed before
+// use) until the list is exhausted.  A tile is (channel << 16) | t, with t as in
+// StepArgs.
 struct BatchStepArgs {
     const ChannelDesc *descs;
     const uint32_t *tiles;

@@ -726,8 +726,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(8, 8))
 // are pulled at K = 2, R = 2) on large ones.  us per step against the best march
 // of the same K: FP32 128 x 64 K = 2 2.1 (4.5), 1024 x 128 3.4 (6.5), 2048 x 768
 // 12.6 (16.5), TRT 3001 x 517 15.0 (18.9); BF16 2048 x 500 K = 1 11.5 (16.1).
-// (The last three 13.9, 16.6 and 11.5 while the rest population and padding went
-// through LDS too and three workgroups, not four, fitted a compute unit.)
+// The rest population stays in a register: with it in LDS three workgroups, not
+// four, fit a compute unit, and the last three take 13.9, 16.6 and 11.5.
 // R = 4 gained 7% in 16-bit storage at 2M nodes and lost 50% in FP32; K = 3 was
 // no faster anywhere.
 constexpr int NODE_BX = 512;
@@ -1199,10 +1199,10 @@ __device__ __forceinline__ void stepk_tile(const StepArgs &a, int x0, int y0, in
 }
 
 // ---------------------------------------------------------------------------
-// The same K steps per launch for FP32 populations, in about 130 vector-ALU
-// instructions per node and step where stepk_tile spends 175 (per launch of
-// 8192 x 2048, K = 3, counting recomputed halo: 127 M against 139 M wave
-// instructions).  The arithmetic is stepk_tile's; what is taken off the
+// The same K steps per launch for FP32 populations, in 147 vector-ALU
+// instructions per node and step where stepk_tile spends 177 (8192 x 2048, K = 3,
+// 512 threads, the recomputed halo included: 116 M against 139 M wave
+// instructions per launch).  The arithmetic is stepk_tile's; what is taken off the
 // vector ALU is everything around it:
 // - The loop body is three iterations, so that the slots of the three-row
 //   rings are compile-time constants: LDS addresses are immediate offsets, and
@@ -1219,7 +1219,7 @@ __device__ __forceinline__ void stepk_tile(const StepArgs &a, int x0, int y0, in
 //   store nothing get an offset past the buffer, which drops the store), so
 //   the wait for a row's loads counts past the stores behind them; loads and
 //   stores share one counter.
-// Registers (about 165) hold it at 3 waves per SIMD, LDS (67 KB at 256
+// Registers (about 165) hold it at 3 waves per SIMD, LDS (61 KB at 256
 // columns, K = 3) at 2, which is why 16-bit storage, bound by vector-ALU issue
 // at 5 waves per SIMD, keeps stepk_tile: there this form measured 101 us per
 // step against 94 (FP16, K = 2) and 134 against 122 with stochastic rounding.
@@ -2282,7 +2282,7 @@ __global__ void __launch_bounds__(512) k_batch_tiles(const ChannelDesc *__restri
 // The batched step with K time steps per launch (the multi-step tile of
 // k_stepk on every tile of every active channel): one workgroup per tile,
 // tiles mapped to XCDs in contiguous ranges, a tile is (channel << 16) |
-// (strip * chunks_k + chunk) with strips of BX - 2H output columns.  With
+// (chunk * strips + strip) with strips of BX - 2H output columns.  With
 // stochastic rounding the K steps take the step counts count .. count + K - 1
 // and the next launch reads count + K, as in k_stepk.
 template <int S, bool TRT, bool SR, int BX, int K, bool TALL = false>

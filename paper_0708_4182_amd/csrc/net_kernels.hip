@@ -516,8 +516,7 @@ __global__ void k_conv1x1_dx(const float *__restrict__ g, const float *__restric
     }
 }
 
-// 1x1 weight and bias gradients: one workgroup per (o, c) entry, and c = cin
-// for the bias; fixed tree.
+// 1x1 weight and bias gradients:
 // dW[o][c] = sum of g[n][o](p) x[n][c](p), db[o] = sum of g[n][o](p) (pair c =
 // cin), in two passes with a fixed order.  Workgroup (b, z, o block) takes share
 // b of the groups of four pixels and the 8 channels from 8 z, four outputs at a
@@ -1957,8 +1956,8 @@ hipError_t up_back(const View &dy, const View &dx, int N, int C, hipStream_t s) 
 template <class TA>
 hipError_t conv1x1(const View &in, const float *w, const float *b, int N, int cin, int cout, float *out,
                    hipStream_t s) {
-    // four pixels per thread from 64 threads per compute unit on, where planes and
-    // rows of pixels are whole aligned groups of four
+    // four pixels per thread from 65,536 threads on (four waves on each of 256 compute
+    // units), where planes and rows of pixels are whole aligned groups of four
     const size_t px = (size_t)N * in.H * in.W;
     if (px >= (size_t)4 * 256 * 256 && (size_t)in.H * in.W % 4 == 0 && in.bs % 4 == 0 && (uintptr_t)in.p % 16 == 0 &&
         (uintptr_t)out % 16 == 0)
